@@ -26,6 +26,7 @@ inline void fill_grid_desc(const int n[3], int dim, double dx, double gamma,
   ph.gm1 = gamma - 1.0;
   ph.dx = dx;
   ph.inv_dx = 1.0 / dx;
+  ph.inv_dx60 = 1.0 / (60.0 * dx);
   ph.cfl = p.cfl;
   ph.c_reg = p.c_reg;
   ph.eps_w = p.eps_weno;

@@ -9,18 +9,20 @@
 //    w u = m / sqrt(rho), w H = (E + p) / sqrt(rho); 1/rho~ = product of the
 //    two 1/sqrt(rho), so the detector needs no division.
 //  * Left eigenvectors (step (2)) are never stored: L x is evaluated as
-//      K = u~ . m(x),  X = b2 x_rho + b1 (x_E - K),  Y = (u~_n x_rho - x_n)/c~
+//      K = x_E - u~ . m(x),  X = b1 (q x_rho + K),  Y = (u~_n x_rho - x_n)/c~
 //      (u-c): (X + Y)/2   entropy: x_rho - X   shear t: (x_t - u~_t x_rho)/c~
 //      (u+c): (X - Y)/2
-//    with b1 = (gamma-1)/c~^2, b2 = b1 |u~|^2/2, and R f likewise from
+//    with b1 = (gamma-1)/c~^2, q = |u~|^2/2, and R f likewise from
 //    S = f_{u-c} + f_0 + f_{u+c}.  Acoustic/entropy right eigenvectors have
 //    unit density component, shear ones are scaled by c~.
 //  * Linear branch (Eq.(34)): because sum_s R^s L^s = I, the face flux is
-//      F = Fc6 + R delta,  delta^s = alpha^s dv^s                 (linear s)
-//                          delta^s = f^s_WENO - L^s Fc6            (WENO s)
+//      F = Fc6 + sum_s R^s alpha^s dv^s
 //    with Fc6 the six-point central flux and dv = L dU5 / 60 the detector
-//    difference of Eq.(31).  The WENO part is added as a correction after
-//    the linear sweep so the common (smooth) path stays short.
+//    difference of Eq.(31); with one speed a0 for the entropy and shear
+//    fields the sum is a0 dU5 / 60 + the acoustic fields' (alpha - a0) dv.
+//    A face that needs the WENO flux gets R f (f the fields' fluxes) minus
+//    this as a correction after the linear pass, so the common (smooth) path
+//    stays short.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -56,6 +58,7 @@ struct KGrid {
 // Physical and scheme constants passed by value.
 struct KPhys {
   double gamma, gm1, dx, inv_dx, cfl;
+  double inv_dx60;     // 1 / (60 dx): scale of the differences of 60 F
   double c_reg, eps_w;
   double eps_thr[3];   // switch threshold C (dx/L_d)^alpha per direction
   int split, hybrid;
@@ -375,10 +378,10 @@ __device__ __forceinline__ void roe_average(const CellRec<NV>& L, const CellRec<
 template <int NV, int DIR>
 __device__ __forceinline__ void project(const Roe<NV>& s, const double (&x)[NV], double (&o)[NV]) {
   constexpr int DIM = NV - 2;
-  double K = 0.0;
+  double K = x[NV - 1];
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) K += s.u[k] * x[1 + k];
-  const double X = s.b2 * x[0] + s.b1 * (x[NV - 1] - K);
+  for (int k = 0; k < DIM; ++k) K -= s.u[k] * x[1 + k];
+  const double X = s.b1 * (s.q * x[0] + K);
   const double Y = (s.u[DIR] * x[0] - x[1 + DIR]) * s.ic;
   o[0] = 0.5 * (X + Y);
   o[1] = x[0] - X;

@@ -399,7 +399,7 @@ __global__ __launch_bounds__(FT_THREADS, WPE) void fused3d_kernel(FusedArgs a, K
     ring_store<NV>(swin, s2, t, c1);
     // face z0 - 1/2 (cells z0-3 .. z0+2): window c0, c1, r0, r1, r2, r3
     const WinSrc<NV> src{c0, c1, r0, r1, r2, r3};
-    zprev = face_linear_l<NV, 2, SPLIT, HYB>(src, ph, ph.eps_thr[2], lfz, Fzp) != 0u;
+    zprev = face_linear_l<NV, 2, SPLIT, HYB>(src, ph, ph.eps_thr[2], lfz, Fzp);
     load_col_raw<NV>(a.Uk, g, ocol, z0 + 3, upre);
   }
   if (halo_need) load_col_raw<NV>(a.Uk, g, hcol, z0, hpre);
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(FT_THREADS, WPE) void fused3d_kernel(FusedArgs a, K
       const int row = t / (FT_X + 1), fx = t % (FT_X + 1);
       const LdsSrc<NV> src{lds_addr(srec, (row + 3) * FP_ROW + fx), 1};
       double F[NV];
-      sgx[t] = face_linear_l<NV, 0, SPLIT, HYB>(src, ph, ph.eps_thr[0], lfx, F) != 0u;
+      sgx[t] = face_linear_l<NV, 0, SPLIT, HYB>(src, ph, ph.eps_thr[0], lfx, F);
 #pragma unroll
       for (int v = 0; v < NV; ++v) sfx[v][t] = F[v];
     }
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(FT_THREADS, WPE) void fused3d_kernel(FusedArgs a, K
       const int col = t % FT_X, fy = t / FT_X;
       const LdsSrc<NV> src{lds_addr(srec, fy * FP_ROW + col + 3), FP_ROW};
       double F[NV];
-      sgy[t] = face_linear_l<NV, 1, SPLIT, HYB>(src, ph, ph.eps_thr[1], lfy, F) != 0u;
+      sgy[t] = face_linear_l<NV, 1, SPLIT, HYB>(src, ph, ph.eps_thr[1], lfy, F);
 #pragma unroll
       for (int v = 0; v < NV; ++v) sfy[v][t] = F[v];
     }
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(FT_THREADS, WPE) void fused3d_kernel(FusedArgs a, K
       // z face z + 1/2: cells z-2, z-1 (ring), z .. z+3 (registers)
       double Fz[NV];
       const ZSrc<NV> src{swin, (z - 2) & 1, (z - 1) & 1, t, r0, r1, r2, r3};
-      const bool zcur = face_linear_l<NV, 2, SPLIT, HYB>(src, ph, ph.eps_thr[2], lfz, Fz) != 0u;
+      const bool zcur = face_linear_l<NV, 2, SPLIT, HYB>(src, ph, ph.eps_thr[2], lfz, Fz);
       const int ix = oy * (FT_X + 1) + ox;
       const int iy = oy * FT_X + ox;
       const long long off = oout + (long long)z * g.stride[2];
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(FT_THREADS, WPE) void fused3d_kernel(FusedArgs a, K
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           const double dU = ((sfx[v][ix] - sfx[v][ix + 1]) + (sfy[v][iy] - sfy[v][iy + FT_X]) +
-                             (Fzp[v] - Fz[v])) * ph.inv_dx;
+                             (Fzp[v] - Fz[v])) * ph.inv_dx60;
           if (OUT == OUT_RK) {
             double r = a.rk_b * (r0.U[v] + dt * dU);
             if (a.rk_a != 0.0) r += a.rk_a * unp[v];

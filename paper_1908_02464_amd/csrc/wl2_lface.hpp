@@ -8,28 +8,21 @@
 
 namespace wl2 {
 
-// 1/x and 1/sqrt(x) from the hardware seeds refined by two Newton steps (the
-// seed error squares each step; the result is within a few ulp, not
-// correctly rounded).
+// 1/x and 1/sqrt(x) from the hardware seeds, refined by one third-order step
+// (the seed error e is cubed: a seed good to 2^-23 gives 2^-67, below the
+// rounding of the last operation; the result is within an ulp or two, not
+// correctly rounded).  One operation (rcp) and two (rsqrt) fewer than two
+// Newton steps, and a shorter chain.
 __device__ __forceinline__ double fast_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-  }
-  return r;
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);  // r (1 + e + e^2)
 }
 
 __device__ __forceinline__ double fast_rsqrt(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const double e = fma(-h * y, y, 0.5);
-    y = fma(y, e, y);
-  }
-  return y;
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);  // y (1 + e/2 + 3 e^2/8)
 }
 
 template <int NV>
@@ -42,7 +35,10 @@ template <int NV>
 __device__ __forceinline__ void make_lrec(const double (&u)[NV], const KPhys& ph, LRec<NV>& r) {
   constexpr int DIM = NV - 2;
   const double iw = fast_rsqrt(u[0]);
-  const double ir = iw * iw;
+  // 1/rho corrected to within rounding: at a high Mach number p is a small
+  // difference of E and the kinetic energy, and magnifies its error
+  const double i2 = iw * iw;
+  const double ir = fma(i2, fma(-u[0], i2, 1.0), i2);
   double m2 = 0.0;
 #pragma unroll
   for (int k = 0; k < DIM; ++k) m2 += u[1 + k] * u[1 + k];
@@ -66,26 +62,28 @@ __device__ __forceinline__ void lflux(const LRec<NV>& r, double (&F)[NV], double
   F[NV - 1] = (r.U[NV - 1] + r.p) * un;
 }
 
+// Roe average of the two cells at the face; EpL, EpR = E + p of each.  With
+// w = sqrt(rho) = 1/iw: 1/(wL + wR) = iwL iwR / (iwL + iwR).
 template <int NV, int DIR>
-__device__ __forceinline__ void roe_light(const LRec<NV>& L, const LRec<NV>& R, const KPhys& ph,
-                                          Roe<NV>& s) {
+__device__ __forceinline__ void roe_light(const LRec<NV>& L, const LRec<NV>& R, double EpL, double EpR,
+                                          const KPhys& ph, Roe<NV>& s) {
   constexpr int DIM = NV - 2;
-  const double wl = L.U[0] * L.iw, wr = R.U[0] * R.iw;
-  const double is = fast_rcp(wl + wr);
+  s.irho = L.iw * R.iw;
+  const double is = s.irho * fast_rcp(L.iw + R.iw);
+  const double wl = L.iw * is, wr = R.iw * is;
   double q = 0.0;
 #pragma unroll
   for (int k = 0; k < DIM; ++k) {
-    s.u[k] = (L.U[1 + k] * L.iw + R.U[1 + k] * R.iw) * is;
+    s.u[k] = L.U[1 + k] * wl + R.U[1 + k] * wr;
     q += s.u[k] * s.u[k];
   }
   s.q = 0.5 * q;
-  s.H = ((L.U[NV - 1] + L.p) * L.iw + (R.U[NV - 1] + R.p) * R.iw) * is;
+  s.H = EpL * wl + EpR * wr;
   const double c2 = ph.gm1 * (s.H - s.q);
   s.ic = fast_rsqrt(c2);
   s.c = c2 * s.ic;
   s.b1 = ph.gm1 * s.ic * s.ic;
   s.b2 = s.b1 * s.q;
-  s.irho = L.iw * R.iw;
 }
 
 // Intermediate quantities of a linear face that its nonlinear correction
@@ -96,137 +94,165 @@ struct FaceState {
   double a[NV], dv[NV], Fc6[NV];
 };
 
+// The sums over the six stencil cells of a face: dU5 (Eq.(31), times 60), the
+// six-point central flux times 60 and the maxima of |u_n - c|, |u_n|,
+// |u_n + c|.  A flux is u_n times a conserved value (plus p): the stencil
+// weight multiplies u_n once and each flux component is one FMA per cell
+// (11 operations per face fewer in 3D than forming every cell's flux and
+// weighting it).
+template <int NV, int DIR>
+struct FaceSums {
+  static constexpr int DIM = NV - 2;
+  double dU[NV], F[NV], ps, am, a0, ap;
+
+  // Cells a (below the face) and b (above it, mirror position), the weights
+  // WF of the flux and WU of U_a - U_b; first: the pair the sums start from.
+  template <bool FIRST>
+  __device__ __forceinline__ void add(const LRec<NV>& a, const LRec<NV>& b, double WF, double WU,
+                                      double& Ea, double& Eb) {
+    const double ua = a.U[1 + DIR] * (a.iw * a.iw), ub = b.U[1 + DIR] * (b.iw * b.iw);
+    const double m_am = fmax(fabs(ua - a.c), fabs(ub - b.c)), m_a0 = fmax(fabs(ua), fabs(ub)),
+                 m_ap = fmax(fabs(ua + a.c), fabs(ub + b.c));
+    Ea = a.U[NV - 1] + a.p;
+    Eb = b.U[NV - 1] + b.p;
+    if (FIRST) {
+      am = m_am;
+      a0 = m_a0;
+      ap = m_ap;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) dU[i] = a.U[i] - b.U[i];
+      F[0] = a.U[1 + DIR] + b.U[1 + DIR];
+      ps = a.p + b.p;
+#pragma unroll
+      for (int k = 0; k < DIM; ++k) F[1 + k] = ua * a.U[1 + k] + ub * b.U[1 + k];
+      F[NV - 1] = ua * Ea + ub * Eb;
+    } else {
+      am = fmax(am, m_am);
+      a0 = fmax(a0, m_a0);
+      ap = fmax(ap, m_ap);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) dU[i] += WU * (a.U[i] - b.U[i]);
+      F[0] += WF * (a.U[1 + DIR] + b.U[1 + DIR]);
+      ps += WF * (a.p + b.p);
+      const double wa = WF * ua, wb = WF * ub;
+#pragma unroll
+      for (int k = 0; k < DIM; ++k) {
+        F[1 + k] += wa * a.U[1 + k];
+        F[1 + k] += wb * b.U[1 + k];
+      }
+      F[NV - 1] += wa * Ea;
+      F[NV - 1] += wb * Eb;
+    }
+  }
+};
+
 // Linear-branch flux of one face from six light records, with its state for
-// a correction; returns the mask of fields whose detector asks for the
-// nonlinear flux.  Cells are requested in the pairs (0,5), (1,4), (2,3) so
-// only two are live at a time.
-template <int NV, int DIR, int SPLIT, int HYB, class Src>
+// a correction, times 60 (the flux difference takes the 1/60 with 1/dx:
+// KPhys::inv_dx60).  Cells are requested in the pairs (0,5), (1,4), (2,3) so
+// only two are live at a time.  ANY: returns whether the detector of some
+// field asks for the nonlinear flux (the largest |dv| decides: the square of
+// a product is monotonic in it, so this agrees with the mask bit for bit);
+// else the mask of those fields.
+// The dissipation R (alpha dv): the entropy and shear fields share one
+// splitting speed a0 and sum_s R^s L^s = 1, so it is a0 dU5 plus the two
+// acoustic fields' (alpha - a0) dv (15 operations in place of 25).
+template <int NV, int DIR, int SPLIT, int HYB, bool ANY, class Src>
 __device__ __forceinline__ unsigned face_linear_st(const Src& src, const KPhys& ph, double eps_thr,
-                                                   const unsigned long long* lfb, double (&Fh)[NV],
+                                                   const unsigned long long* lfb, double (&F60)[NV],
                                                    FaceState<NV>& st) {
+  constexpr int DIM = NV - 2;
   const int split = SPLIT >= 0 ? SPLIT : ph.split;
   const int hybrid = HYB >= 0 ? HYB : ph.hybrid;
-  double dU5[NV], Fc6[NV];
-  double am, a0, ap;
-  LRec<NV> c2, c3;
+  FaceSums<NV, DIR> f;
+  double Ea, Eb;
   {
     LRec<NV> c0, c5;
     src.get(0, c0);
     src.get(5, c5);
-    double F0[NV], F5[NV], u0, u5;
-    lflux<NV, DIR>(c0, F0, u0);
-    lflux<NV, DIR>(c5, F5, u5);
-    am = fmax(fabs(u0 - c0.c), fabs(u5 - c5.c));
-    a0 = fmax(fabs(u0), fabs(u5));
-    ap = fmax(fabs(u0 + c0.c), fabs(u5 + c5.c));
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      dU5[i] = c0.U[i] - c5.U[i];
-      Fc6[i] = F0[i] + F5[i];
-    }
+    f.template add<true>(c0, c5, 1.0, 1.0, Ea, Eb);
   }
   {
     LRec<NV> c1, c4;
     src.get(1, c1);
     src.get(4, c4);
-    double F1[NV], F4[NV], u1, u4;
-    lflux<NV, DIR>(c1, F1, u1);
-    lflux<NV, DIR>(c4, F4, u4);
-    am = fmax(am, fmax(fabs(u1 - c1.c), fabs(u4 - c4.c)));
-    a0 = fmax(a0, fmax(fabs(u1), fabs(u4)));
-    ap = fmax(ap, fmax(fabs(u1 + c1.c), fabs(u4 + c4.c)));
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      dU5[i] += 5.0 * (c4.U[i] - c1.U[i]);
-      Fc6[i] -= 8.0 * (F1[i] + F4[i]);
-    }
+    f.template add<false>(c1, c4, -8.0, -5.0, Ea, Eb);
   }
+  LRec<NV> c2, c3;
   src.get(2, c2);
   src.get(3, c3);
-  {
-    double F2[NV], F3[NV], u2, u3;
-    lflux<NV, DIR>(c2, F2, u2);
-    lflux<NV, DIR>(c3, F3, u3);
-    am = fmax(am, fmax(fabs(u2 - c2.c), fabs(u3 - c3.c)));
-    a0 = fmax(a0, fmax(fabs(u2), fabs(u3)));
-    ap = fmax(ap, fmax(fabs(u2 + c2.c), fabs(u3 + c3.c)));
+  f.template add<false>(c2, c3, 37.0, 10.0, Ea, Eb);
+  f.F[1 + DIR] += f.ps;
+  Roe<NV> s;
+  roe_light<NV, DIR>(c2, c3, Ea, Eb, ph, s);
+  double am = f.am, a0 = f.a0, ap = f.ap;
+  if (split == SPLIT_ROE) {
+    am = fabs(s.u[DIR] - s.c);
+    a0 = fabs(s.u[DIR]);
+    ap = fabs(s.u[DIR] + s.c);
+  } else if (split != SPLIT_LLF) {
+    am = __longlong_as_double((long long)lfb[0]);
+    a0 = __longlong_as_double((long long)lfb[1]);  // one speed for the fields between
+    ap = __longlong_as_double((long long)lfb[NV - 1]);
+  }
+  // dv = L dU5 / 60 and Fc6 enter scaled by 60; the detector takes the 1/60
+  constexpr double k60 = 1.0 / 60.0;
+  double dv[NV];
+  project<NV, DIR>(s, f.dU, dv);
+  const double irho60 = s.irho * k60;
+  unsigned weno = 0;
+  if (hybrid == HYB_WENO_ONLY) {
+    weno = (1u << NV) - 1u;
+  } else if (hybrid != HYB_LINEAR_ONLY) {
+    double vmax = fabs(dv[0]);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      dU5[i] += 10.0 * (c2.U[i] - c3.U[i]);
-      Fc6[i] += 37.0 * (F2[i] + F3[i]);  // 60 Fc6: the 1/60 is applied below
+    for (int k = 1; k < NV; ++k) vmax = fmax(vmax, fabs(dv[k]));
+    const double tm = vmax * irho60;
+    const bool any = !(tm * tm < eps_thr);  // Eq.(30), (35)
+    if (ANY) {
+      weno = any ? 1u : 0u;
+    } else if (hybrid == HYB_PER_FACE) {
+      weno = any ? ((1u << NV) - 1u) : 0u;
+    } else {
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const double t = dv[k] * irho60;
+        const double sig = t * t;
+        if (!(sig < eps_thr)) weno |= 1u << k;
+      }
     }
   }
-  Roe<NV> s;
-  roe_light<NV, DIR>(c2, c3, ph, s);
-  double a[NV];
-  if (split == SPLIT_LLF) {
-    a[0] = am;
+  const double g = (am - a0) * dv[0], h = (ap - a0) * dv[NV - 1];
+  const double S = g + h, D = s.c * (h - g);
 #pragma unroll
-    for (int k = 1; k < NV - 1; ++k) a[k] = a0;
-    a[NV - 1] = ap;
-  } else if (split == SPLIT_ROE) {
-    a[0] = fabs(s.u[DIR] - s.c);
+  for (int i = 0; i < NV; ++i) F60[i] = f.F[i] + a0 * f.dU[i];
+  F60[0] += S;
 #pragma unroll
-    for (int k = 1; k < NV - 1; ++k) a[k] = fabs(s.u[DIR]);
-    a[NV - 1] = fabs(s.u[DIR] + s.c);
-  } else {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) a[k] = __longlong_as_double((long long)lfb[k]);
-  }
-  // dv = L dU5 / 60 and Fc6 enter scaled by 60; the 1/60 is folded into
-  // the detector scale, the splitting speeds and the final flux
-  constexpr double k60 = 1.0 / 60.0;
-  double dv[NV], d[NV], a60[NV];
-  project<NV, DIR>(s, dU5, dv);
-  const double irho60 = s.irho * k60;
-  if (split == SPLIT_LLF) {
-    const double am60 = a[0] * k60, a060 = a[1] * k60, ap60 = a[NV - 1] * k60;
-    a60[0] = am60;
-#pragma unroll
-    for (int k = 1; k < NV - 1; ++k) a60[k] = a060;
-    a60[NV - 1] = ap60;
-  } else {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) a60[k] = a[k] * k60;
-  }
-  unsigned weno = 0;
-  double smax = 0.0;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const double t = dv[k] * irho60;
-    const double sig = t * t;  // Eq.(30)
-    smax = fmax(smax, sig);
-    if (!(sig < eps_thr)) weno |= 1u << k;
-    d[k] = a60[k] * dv[k];
-  }
-  if (hybrid == HYB_PER_FACE) weno = (smax < eps_thr) ? 0u : ((1u << NV) - 1u);
-  else if (hybrid == HYB_WENO_ONLY) weno = (1u << NV) - 1u;
-  else if (hybrid == HYB_LINEAR_ONLY) weno = 0u;
-  double Rd[NV];
-  back_project<NV, DIR>(s, d, Rd);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) Fh[i] = Fc6[i] * k60 + Rd[i];
+  for (int k = 0; k < DIM; ++k) F60[1 + k] += s.u[k] * S;
+  F60[1 + DIR] += D;
+  F60[NV - 1] += s.H * S;
+  F60[NV - 1] += s.u[DIR] * D;
   // the state in the paper's units for a nonlinear correction (dead code,
   // removed by the compiler, where the caller drops it)
   st.s = s;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    st.a[k] = a[k];
+    st.a[k] = k == 0 ? am : (k == NV - 1 ? ap : a0);
     st.dv[k] = dv[k] * k60;
-    st.Fc6[k] = Fc6[k] * k60;
+    st.Fc6[k] = f.F[k] * k60;
   }
   return weno;
 }
 
-// Linear-branch flux of one face from six light records; returns the mask
-// of fields whose detector asks for the nonlinear flux.  `src.get(m, rec)`
-// supplies stencil cell m = 0..5 (j-2 .. j+3).  SPLIT / HYB: compile-time
-// splitting and switch modes, or -1 to read them from ph at run time.
+// Linear-branch flux (times 60) of one face from six light records; returns
+// whether some field's detector asks for the nonlinear flux.  `src.get(m,
+// rec)` supplies stencil cell m = 0..5 (j-2 .. j+3).  SPLIT / HYB:
+// compile-time splitting and switch modes, or -1 to read them from ph at run
+// time.
 template <int NV, int DIR, int SPLIT, int HYB, class Src>
-__device__ __forceinline__ unsigned face_linear_l(const Src& src, const KPhys& ph, double eps_thr,
-                                                  const unsigned long long* lfb, double (&Fh)[NV]) {
+__device__ __forceinline__ bool face_linear_l(const Src& src, const KPhys& ph, double eps_thr,
+                                              const unsigned long long* lfb, double (&F60)[NV]) {
   FaceState<NV> st;
-  return face_linear_st<NV, DIR, SPLIT, HYB>(src, ph, eps_thr, lfb, Fh, st);
+  return face_linear_st<NV, DIR, SPLIT, HYB, true>(src, ph, eps_thr, lfb, F60, st) != 0u;
 }
 
 // Index of a line position clamped to [-3, n+2] and mapped through the
@@ -288,15 +314,30 @@ __device__ __forceinline__ double weno_l2is_lr(double fm2, double fm1, double f0
   return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * fast_rcp((a0 + a1) + (a2 + a3));
 }
 
-// Nonlinear (WENO-L2IS) correction of one flagged face, field by field:
-// for each field k in `mask`, the left eigenvector row L^k is formed, the six
-// stencil cells are projected (Eq.(20)), split (Eq.(21)) and reconstructed
-// (Eq.(22)-(23)); the change with respect to the linear flux of that field is
-// back-projected (Eq.(24)).  Only one row and twelve split values are live.
+// Nonlinear (WENO-L2IS) flux of one flagged face, field by field: for each
+// field k in `mask`, the left eigenvector row L^k is formed, the six stencil
+// cells are projected (Eq.(20)), split (Eq.(21)) and reconstructed
+// (Eq.(22)-(23)); the other fields keep their linear flux.  The fields'
+// fluxes are back-projected (Eq.(24)), and the correction is the difference
+// from the linear face flux: where that is large and the WENO flux small
+// (ambient cells next to a Mach 2000 jet), the sum of both keeps the
+// rounding of the small one.  Only one row and twelve split values are live.
 // W: the weighting (W_*) fixed at compile time, or -1 to read ph.weights.
-template <int NV, int DIR, int W, class Src>
+template <int NV>
+__device__ __forceinline__ double dot2(const double (&r)[NV], const double (&x)[NV], int i) {
+  double a = r[0] * x[0];  // the order of dot
+  a += r[i] * x[i];
+  return a;
+}
+
+// K: the field where it is known at compile time, else -1.  A shear row has
+// two entries, so its products with zero (which change no bit of the sum) are
+// left out.
+template <int NV, int DIR, int W, int K, class Src>
 __device__ __forceinline__ double lean_field_row(const Src& src, const double (&r)[NV], const Roe<NV>& s,
-                                                 double al, double dvk, double LFk, const KPhys& ph) {
+                                                 double al, double dvk, const KPhys& ph) {
+  constexpr bool SHEAR = K >= 2 && K < NV - 1;
+  constexpr int comp = SHEAR ? (K - 2 < DIR ? K - 2 : K - 1) : 0;  // its momentum component
   double fp[6], fm[6];
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
@@ -304,25 +345,24 @@ __device__ __forceinline__ double lean_field_row(const Src& src, const double (&
     src.get(m, cm);
     double F[NV], un;
     lflux<NV, DIR>(cm, F, un);
-    const double vv = dot<NV>(r, cm.U);
-    const double gg = dot<NV>(r, F);
+    const double vv = SHEAR ? dot2<NV>(r, cm.U, 1 + comp) : dot<NV>(r, cm.U);
+    const double gg = SHEAR ? dot2<NV>(r, F, 1 + comp) : dot<NV>(r, F);
     fp[m] = 0.5 * (gg + al * vv);
     fm[m] = 0.5 * (gg - al * vv);
   }
   const double t = dvk * s.irho;
   const double lam = ph.c_reg * (t * t);  // Eq.(32)
   const int wts = W >= 0 ? W : ph.weights;
-  const double fw = weno_l2is_lr(fp[0], fp[1], fp[2], fp[3], fp[4], lam, ph.eps_w, wts) +
-                    weno_l2is_lr(fm[5], fm[4], fm[3], fm[2], fm[1], lam, ph.eps_w, wts);
-  return fw - (LFk + al * dvk);
+  return weno_l2is_lr(fp[0], fp[1], fp[2], fp[3], fp[4], lam, ph.eps_w, wts) +
+         weno_l2is_lr(fm[5], fm[4], fm[3], fm[2], fm[1], lam, ph.eps_w, wts);
 }
 
 template <int NV, int DIR, int K, int W, class Src>
 __device__ __forceinline__ double lean_field(const Src& src, const Roe<NV>& s, double al, double dvk,
-                                             double LFk, const KPhys& ph) {
+                                             const KPhys& ph) {
   double r[NV];
   left_row<NV, DIR, K>(s, r);
-  return lean_field_row<NV, DIR, W>(src, r, s, al, dvk, LFk, ph);
+  return lean_field_row<NV, DIR, W, K>(src, r, s, al, dvk, ph);
 }
 
 // Row k of L for a field k known only at run time: each candidate row with
@@ -354,19 +394,23 @@ __device__ __forceinline__ void left_row_rt(const Roe<NV>& s, int k, double (&r)
   for (int i = 0; i < NV; ++i) r[i] = acoustic ? ac[i] : (k == 1 ? en[i] : sh[i]);
 }
 
+// The change of the face's flux for the fields in mask: R f - F60 / 60.
 template <int NV, int DIR, int W = -1, class Src>
 __device__ __forceinline__ void lean_correction(const Src& src, unsigned mask, const FaceState<NV>& st,
-                                                const KPhys& ph, double (&dF)[NV]) {
-  double LF[NV], del[NV];
+                                                const double (&F60)[NV], const KPhys& ph,
+                                                double (&dF)[NV]) {
+  double LF[NV], f[NV];
   project<NV, DIR>(st.s, st.Fc6, LF);
-#define WL2_LF(K)                                                                            \
-  if constexpr (K < NV) {                                                                    \
-    del[K] = ((mask >> K) & 1u) ? lean_field<NV, DIR, K, W>(src, st.s, st.a[K], st.dv[K], LF[K], ph) \
-                                : 0.0;                                                       \
+#define WL2_LF(K)                                                                                 \
+  if constexpr (K < NV) {                                                                         \
+    f[K] = ((mask >> K) & 1u) ? lean_field<NV, DIR, K, W>(src, st.s, st.a[K], st.dv[K], ph)       \
+                              : LF[K] + st.a[K] * st.dv[K];                                       \
   }
   WL2_LF(0) WL2_LF(1) WL2_LF(2) WL2_LF(3) WL2_LF(4)
 #undef WL2_LF
-  back_project<NV, DIR>(st.s, del, dF);
+  back_project<NV, DIR>(st.s, f, dF);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) dF[v] -= F60[v] * (1.0 / 60.0);
 }
 
 // The six stencil cells of the face of cell (x, y, z) along DIR below it
@@ -413,9 +457,9 @@ __device__ __forceinline__ void face_delta(const double* U, const KGrid& g, cons
   const WinSrc<NV> src{w[0], w[1], w[2], w[3], w[4], w[5]};
   double Flin[NV];
   FaceState<NV> st;
-  const unsigned mask = face_linear_st<NV, DIR, SPLIT, HYB>(src, ph, ph.eps_thr[DIR], lfb, Flin, st);
+  const unsigned mask = face_linear_st<NV, DIR, SPLIT, HYB, false>(src, ph, ph.eps_thr[DIR], lfb, Flin, st);
   if (mask) {
-    lean_correction<NV, DIR, W>(src, mask, st, ph, dF);
+    lean_correction<NV, DIR, W>(src, mask, st, Flin, ph, dF);
   } else {
 #pragma unroll
     for (int v = 0; v < NV; ++v) dF[v] = 0.0;
@@ -436,7 +480,7 @@ __device__ __forceinline__ void face_delta_field(const double* U, const KGrid& g
   const WinSrc<NV> src{w[0], w[1], w[2], w[3], w[4], w[5]};
   double Flin[NV];
   FaceState<NV> st;
-  const unsigned mask = face_linear_st<NV, DIR, SPLIT, HYB>(src, ph, ph.eps_thr[DIR], lfb, Flin, st);
+  const unsigned mask = face_linear_st<NV, DIR, SPLIT, HYB, false>(src, ph, ph.eps_thr[DIR], lfb, Flin, st);
   double LF[NV];
   project<NV, DIR>(st.s, st.Fc6, LF);
   double al = st.a[0], dvk = st.dv[0], LFk = LF[0];
@@ -446,17 +490,19 @@ __device__ __forceinline__ void face_delta_field(const double* U, const KGrid& g
     dvk = j == k ? st.dv[j] : dvk;
     LFk = j == k ? LF[j] : LFk;
   }
-  double mine = 0.0;
+  double mine = LFk + al * dvk;
   if ((mask >> k) & 1u) {
     double r[NV];
     left_row_rt<NV, DIR>(st.s, k, r);
-    mine = lean_field_row<NV, DIR, W>(src, r, st.s, al, dvk, LFk, ph);
+    mine = lean_field_row<NV, DIR, W, -1>(src, r, st.s, al, dvk, ph);
   }
-  double del[NV];
+  double f[NV];
 #pragma unroll
-  for (int j = 0; j < NV; ++j) del[j] = __shfl(mine, lane0 + j, 64);
+  for (int j = 0; j < NV; ++j) f[j] = __shfl(mine, lane0 + j, 64);
   if (mask) {
-    back_project<NV, DIR>(st.s, del, dF);
+    back_project<NV, DIR>(st.s, f, dF);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) dF[v] -= Flin[v] * (1.0 / 60.0);
   } else {
 #pragma unroll
     for (int v = 0; v < NV; ++v) dF[v] = 0.0;

@@ -199,19 +199,19 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
     }
     __syncthreads();
     double Fx[NV];
-    const unsigned mx =
+    const bool mx =
         face_linear_l<NV, 0, SPLIT, HYB>(RowSrc<NV>{buf, lane}, ph, ph.eps_thr[0], lfx, Fx);
     double Fr[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) Fr[v] = __shfl_down(Fx[v], 1, RW);
-    const unsigned mxr = __shfl_down(mx, 1, RW);
+    const int mxr = __shfl_down((int)mx, 1, RW);
     const unsigned cm = own ? ((mx ? 1u : 0u) | (mxr ? 2u : 0u)) : 0u;
     list_append(a, oxy, cm);
     if (own) {
       double un[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const double dU = (Fx[v] - Fr[v]) * ph.inv_dx;
+        const double dU = (Fx[v] - Fr[v]) * ph.inv_dx60;
         if (OUT == OUT_RK) {
           double r = a.rk_b * (own_rec.U[v] + dt * dU);
           if (a.rk_a != 0.0) r += a.rk_a * unp[v];
@@ -262,7 +262,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       ring_put<NV>(ring, (y0 - 1) & 1, lane, cm1);
       // face y0 - 1/2: cells y0-3 .. y0+2
       const LRec<NV> wp[6] = {cm3, cm2, cm1, r0, r1, r2};
-      yprev = face_linear_l<NV, 1, SPLIT, HYB>(Win6Src<NV>{wp}, ph, ph.eps_thr[1], lfy, Fyp) != 0u;
+      yprev = face_linear_l<NV, 1, SPLIT, HYB>(Win6Src<NV>{wp}, ph, ph.eps_thr[1], lfy, Fyp);
       row_load_raw<NV, YS>(a.Uk, g, oxy, y0 + 4, upre);
       if (halo) row_load_raw<NV, YS>(a.Uk, g, hxy, y0, hpre);
     }
@@ -281,7 +281,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       __builtin_amdgcn_s_setprio(0);
       // x face on the left of column x0+lane (cells x-3 .. x+2 = slots lane .. lane+5)
       double Fx[NV];
-      const unsigned mx =
+      const bool mx =
           face_linear_l<NV, 0, SPLIT, HYB>(RowSrc<NV>{buf, lane}, ph, ph.eps_thr[0], lfx, Fx);
       const long long off = oxy + (long long)y * g.stride[1];
       double unp[NV] = {};
@@ -293,11 +293,11 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       double Fy[NV];
       const bool ycur = face_linear_l<NV, 1, SPLIT, HYB>(
                             RingSrc<NV>{ring, (y - 2) & 1, (y - 1) & 1, lane, r0, r1, r2, r3}, ph,
-                            ph.eps_thr[1], lfy, Fy) != 0u;
+                            ph.eps_thr[1], lfy, Fy);
       double Fr[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) Fr[v] = __shfl_down(Fx[v], 1, RW);
-      const unsigned mxr = __shfl_down(mx, 1, RW);
+      const int mxr = __shfl_down((int)mx, 1, RW);
       const unsigned cm =
           own ? ((mx ? 1u : 0u) | (mxr ? 2u : 0u) | (yprev ? 4u : 0u) | (ycur ? 8u : 0u)) : 0u;
       list_append(a, off, cm);
@@ -310,7 +310,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
         double un[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          const double dU = ((Fx[v] - Fr[v]) + (Fyp[v] - Fy[v])) * ph.inv_dx;
+          const double dU = ((Fx[v] - Fr[v]) + (Fyp[v] - Fy[v])) * ph.inv_dx60;
           if (OUT == OUT_RK) {
             double r = a.rk_b * (r0.U[v] + dt * dU);
             if (a.rk_a != 0.0) r += a.rk_a * unp[v];
