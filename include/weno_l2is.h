@@ -188,9 +188,9 @@ int weno_l2is_step(weno_l2is_ctx *ctx, double *U, double dt);
  * The simulated time is kept on the device and read by weno_l2is_time.
  * The result equals n_steps calls of weno_l2is_step with the clock rule, bit
  * for bit; internally the CFL maximum of a step is folded out of the
- * previous step's last stage, and 1D grids of up to 1024 cells (not with
- * global Lax-Friedrichs splitting) run all steps in one single-workgroup
- * launch.  Asynchronous on the context's stream. */
+ * previous step's last stage, and 1D grids (not with global Lax-Friedrichs
+ * splitting) run a whole step in one launch, up to 504 cells all steps of
+ * the call.  Asynchronous on the context's stream. */
 int weno_l2is_advance(weno_l2is_ctx *ctx, double *U, int n_steps,
                       double t_end);
 

@@ -38,6 +38,7 @@ struct weno_l2is_ctx {
   double* fo3 = nullptr;           // 3D: each face's change (face-once corrections)
   unsigned int* flist = nullptr;   // 3D hybrid: faces needing the WENO flux
   unsigned int* counts = nullptr;  // 3D: entries each stage-kernel workgroup listed
+  LineCtl* line = nullptr;         // 1D: clock and CFL sets of the whole-step launches
   double* inflow = nullptr;        // x- inflow side: ghost state [nvar][ny*nz]
   double* ygh = nullptr;           // y state sides: ghost rows of both, [side][layer][nvar][nx]
   bool inflow_set = false;         // weno_l2is_set_inflow has been called
@@ -252,11 +253,16 @@ hipError_t launch_lf(const weno_l2is_ctx* c, const double* U, double tc) {
 
 bool use_fused(const weno_l2is_ctx* c) { return c->dim == 3 && c->path != WL2_PATH_SWEEPS; }
 bool use_row(const weno_l2is_ctx* c) { return c->dim <= 2 && c->path != WL2_PATH_SWEEPS; }
-// advance() of a small 1D grid runs in one single-workgroup launch (not with
-// global Lax-Friedrichs speeds, which need a grid-wide reduction per stage)
-bool use_row_steps(const weno_l2is_ctx* c) {
-  if (c->p.bc[0] == WL2_BC_INFLOW) return false;  // its time step has no inflow speed
-  return c->dim == 1 && use_row(c) && c->n[0] <= ROW_STEPS_MAX_CELLS && c->p.split != WL2_SPLIT_LF;
+// advance() of a 1D grid keeps a step's stages on the chip (not with global
+// Lax-Friedrichs speeds, which need a grid-wide reduction per stage).
+bool use_line(const weno_l2is_ctx* c) {
+  return c->dim == 1 && use_row(c) && c->p.split != WL2_SPLIT_LF;
+}
+
+// Up to 504 cells every step runs in one workgroup (whose time step knows no
+// inflow speed), else one launch per step.
+bool use_line_steps(const weno_l2is_ctx* c) {
+  return c->n[0] <= LINE_STEPS_MAX_CELLS && c->p.bc[0] != WL2_BC_INFLOW;
 }
 
 // 2D grids from this many cells correct their flagged faces once each (two
@@ -591,7 +597,7 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
     ok = hipMalloc(&c->fo3, sizeof(double) * fused3d_face_doubles(c->n)) == hipSuccess;
   if (ok && hyb3)
     ok = hipMalloc(&c->flist, sizeof(unsigned int) * fused3d_flist_entries(c->n)) == hipSuccess;
-  // 3D: per-workgroup counts of the correction list and their prefix sums
+  if (ok && c->dim == 1) ok = hipMalloc(&c->line, LINE_CTL_BYTES) == hipSuccess;
   if (ok && p->bc[0] == WL2_BC_INFLOW)
     ok = hipMalloc(&c->inflow, sizeof(double) * c->nvar * (size_t)ny * nz) == hipSuccess;
   if (ok) c->g.inflow = c->inflow;
@@ -599,6 +605,7 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
   if (ok && has_state_sides(p, c->dim))
     ok = hipMalloc(&c->ygh, sizeof(double) * 2 * 3 * 4 * (size_t)nx) == hipSuccess;
   if (ok) fill_desc(c);
+  // 3D: per-workgroup counts of the correction lists and their prefix sums
   // (cell list: counts and offsets; face lists: counts and offsets over
   // three directions)
   if (ok && c->dim == 3)
@@ -615,6 +622,7 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
     (void)hipFree(c->fo3);
     (void)hipFree(c->flist);
     (void)hipFree(c->counts);
+    (void)hipFree(c->line);
     (void)hipFree(c->inflow);
     (void)hipFree(c->ygh);
     (void)hipFree(c->ctl);
@@ -639,6 +647,7 @@ void weno_l2is_destroy(weno_l2is_ctx* c) {
   (void)hipFree(c->fo3);
   (void)hipFree(c->flist);
   (void)hipFree(c->counts);
+  (void)hipFree(c->line);
   (void)hipFree(c->inflow);
   (void)hipFree(c->ygh);
   (void)hipFree(c->ctl);
@@ -805,14 +814,16 @@ int weno_l2is_advance(weno_l2is_ctx* c, double* U, int n_steps, double t_end) {
   if (!c || !U) return WL2_E_NULL;
   if (n_steps < 0 || !(t_end > 0.0) || !std::isfinite(t_end)) return WL2_E_PARAM;
   if (inflow_missing(c)) return WL2_E_BC;
+  if (use_line(c) && !use_line_steps(c)) {
+    TimedLaunch tl(c, "line_step");
+    return hip_err(line_advance(U, c->U1, c->line, c->ctl, c->p.cfl * c->dx, c->inflow_speed, n_steps, t_end,
+                                c->g, c->ph, c->stream));
+  }
   hipLaunchKernelGGL(set_t_end_kernel, dim3(1), dim3(64), 0, c->stream, c->ctl, t_end);
   hipError_t e = hipGetLastError();
-  // small 1D grids: every step in one single-workgroup launch
-  if (e == hipSuccess && use_row_steps(c)) {
-    TimedLaunch tl(c, "row1d_steps");
-    return hip_err(row1d_steps(U, c->U1, c->U2, c->ctl, c->list, c->p.cfl * c->dx, n_steps,
-                               c->p.split == WL2_SPLIT_LLF && c->p.hybrid == WL2_HYB_PER_FIELD,
-                               c->g, c->ph, c->stream));
+  if (e == hipSuccess && use_line(c)) {
+    TimedLaunch tl(c, "line_steps");
+    return hip_err(line_steps(U, c->ctl, c->p.cfl * c->dx, n_steps, c->g, c->ph, c->stream));
   }
   // fused 3D and row 1D/2D paths: the last stage of a step also reduces the
   // CFL speed of the new state (its cells are in registers there), so every

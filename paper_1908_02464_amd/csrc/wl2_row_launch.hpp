@@ -46,14 +46,17 @@ hipError_t row_reset(const RowLaunch& L);
 hipError_t row_launch(const RowLaunch& L);
 hipError_t row_fix(const RowLaunch& L);
 
-// Small 1D grids: n_steps clock steps of U (SSP-RK3, device CFL dt, the
-// clock rule of the multi-launch path) in one single-workgroup launch of
-// eight wavefronts (measured per step against seven launches: 200 cells
-// 19 vs 33 us, 800 cells 26 vs 34 us, 1024 cells 31 vs 33 us, 1600 cells
-// 38 vs 35 us; sixteen wavefronts spill).
-constexpr int ROW_STEPS_MAX_CELLS = 1024;
-hipError_t row1d_steps(double* U, double* U1, double* U2, StepCtl* ctl, unsigned long long* list,
-                       double cfl_dx, int n_steps, int fast, const KGrid& g, const KPhys& ph,
-                       hipStream_t stream);
+// 1D grids: n_steps clock steps of U (SSP-RK3, device CFL dt, the clock rule
+// of finalize_dt_kernel; not with global LF splitting, whose speeds need a
+// grid-wide reduction per stage).  line_steps: up to 504 cells, one
+// single-workgroup launch for all steps (no inflow side).  line_advance: any
+// grid, one launch per step; tmp: a second state array.
+constexpr int LINE_STEPS_MAX_CELLS = 504;
+constexpr size_t LINE_CTL_BYTES = 3 * CFL_SLOTS * 128 + 128;
+struct LineCtl;
+hipError_t line_steps(double* U, StepCtl* ctl, double cfl_dx, int n_steps, const KGrid& g, const KPhys& ph,
+                      hipStream_t stream);
+hipError_t line_advance(double* U, double* tmp, LineCtl* lc, StepCtl* ctl, double cfl_dx, double s_floor,
+                        int n_steps, double t_end, const KGrid& g, const KPhys& ph, hipStream_t stream);
 
 }  // namespace wl2
