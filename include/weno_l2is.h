@@ -118,7 +118,8 @@ int weno_l2is_params_default(weno_l2is_params *p, int nx, int ny, int nz,
 /* Create a solver context for one grid.  hip_stream: hipStream_t (NULL =
  * the null stream); all of the context's work is enqueued there.  Allocates
  * the two RK stage buffers, one accumulator (per-direction path), the
- * correction list (8 bytes per cell), a 6.4 KB control block, for 2D
+ * correction list (8 bytes per cell), a 6.4 KB control block (6 KB more for
+ * 2D grids with global LF splitting, 12.4 KB for 1D grids), for 2D
  * grids of 131072 cells or more the face-once correction buffers (68 bytes
  * per cell), and for 3D grids a face buffer (120 bytes per cell) where the
  * corrections compute each face once: with every face WENO (LLF

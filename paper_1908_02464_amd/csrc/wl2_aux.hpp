@@ -88,35 +88,49 @@ struct YGhostRule {
   double geom[4];
 };
 
+// The state of the ghost at column x, row y (outside the grid, at most three
+// rows) of a y state side, at time t.
+__device__ __forceinline__ void yghost_value(const double* __restrict__ U, const KGrid& g, double t,
+                                             double dx, const YGhostRule& rule, long long x, int y,
+                                             double (&u)[4]) {
+  const long long nx = g.n[0];
+  const int ny = g.n[1], side = y < 0 ? 0 : 1;
+  const int kind = side ? g.bc_hi[1] : g.bc_lo[1];
+  const double xc = ((double)x + 0.5) * dx;
+  if (kind == BC_STATE_FRONT) {
+    const double yc = ((double)y + 0.5) * dx;
+    const bool left = xc < rule.geom[1] + rule.geom[2] * yc + rule.geom[3] * t;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) u[v] = left ? rule.state[0][v] : rule.state[1][v];
+  } else if (xc < rule.geom[0]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) u[v] = rule.state[0][v];
+  } else {
+    const long long row = side ? 2 * ny - 1 - y : -1 - y;  // the mirror row
+#pragma unroll
+    for (int v = 0; v < 4; ++v) u[v] = U[v * g.ncell + row * nx + x];
+    u[2] = -u[2];
+  }
+}
+
+// The time the ghosts of a stage are taken at: t0 + tc dt (tc < 0: the clock's t).
+__device__ __forceinline__ double yghost_time(const StepCtl* ctl, double tc) {
+  return tc < 0.0 ? ctl->t : ctl->t0 + tc * ctl->dt;
+}
+
 // Ghost value i of the 2 x 3 x nx (side, layer, column) of the y sides.
 __device__ __forceinline__ void ghost_fill_item(const double* __restrict__ U, const KGrid& g,
                                                 const StepCtl* ctl, double tc, double dx,
                                                 const YGhostRule& rule, double* lo, double* hi,
                                                 long long i) {
-  const long long nx = g.n[0], ny = g.n[1];
+  const long long nx = g.n[0];
   const int side = (int)(i / (3 * nx));
   const int layer = (int)((i / nx) % 3);
   const long long x = i % nx;
-  const int kind = side ? g.bc_hi[1] : g.bc_lo[1];
   double* b = side ? hi : lo;
-  if (kind < BC_STATE_WALL || b == nullptr) return;
-  const double xc = ((double)x + 0.5) * dx;
+  if ((side ? g.bc_hi[1] : g.bc_lo[1]) < BC_STATE_WALL || b == nullptr) return;
   double u[4];
-  if (kind == BC_STATE_FRONT) {
-    const double t = tc < 0.0 ? ctl->t : ctl->t0 + tc * ctl->dt;
-    const double yc = ((double)(side ? ny + layer : -1 - layer) + 0.5) * dx;
-    const int s = xc < rule.geom[1] + rule.geom[2] * yc + rule.geom[3] * t ? 0 : 1;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) u[v] = rule.state[s][v];
-  } else if (xc < rule.geom[0]) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) u[v] = rule.state[0][v];
-  } else {
-    const long long row = side ? ny - 1 - layer : layer;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) u[v] = U[v * g.ncell + row * nx + x];
-    u[2] = -u[2];
-  }
+  yghost_value(U, g, yghost_time(ctl, tc), dx, rule, x, side ? g.n[1] + layer : -1 - layer, u);
 #pragma unroll
   for (int v = 0; v < 4; ++v) b[((long long)layer * 4 + v) * nx + x] = u[v];
 }
@@ -130,11 +144,72 @@ __device__ __forceinline__ void ghost_fill_item(const double* __restrict__ U, co
 }
 
 // Program the device clock target (enqueued, no host synchronisation) and
-// clear the running CFL maximum.
-[[maybe_unused]] static __global__ void set_t_end_kernel(StepCtl* ctl, double t_end) {
+// clear the running CFL maximum and, where given, the three sets of LF slots
+// that the stages of the call pass on.
+[[maybe_unused]] static __global__ void set_t_end_kernel(StepCtl* ctl, double t_end, LfSlot* sets) {
+  if (sets != nullptr && threadIdx.x < 3 * LF_SLOTS) sets[threadIdx.x] = LfSlot{};
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     ctl->t_end = t_end;
     cfl_clear(ctl);  // a maximum left by an earlier call is stale
+  }
+}
+
+// |u_d - c|, |u_d|, |u_d + c| of one state folded into mx (one definition for
+// the reduction and for the stage kernels that fold the state they write).
+template <int NV>
+__device__ __forceinline__ void lf_fold_cell(const double (&u)[NV], double gamma, double (&mx)[NV - 2][3]) {
+  constexpr int DIM = NV - 2;
+  const double ir = 1.0 / u[0];
+  double vel[DIM], mu = 0.0;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) {
+    vel[k] = u[1 + k] * ir;
+    mu += u[1 + k] * vel[k];
+  }
+  const double p = (gamma - 1.0) * (u[NV - 1] - 0.5 * mu);
+  const double cs = sqrt(gamma * p * ir);
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    mx[d][0] = fmax(mx[d][0], fabs(vel[d] - cs));
+    mx[d][1] = fmax(mx[d][1], fabs(vel[d]));
+    mx[d][2] = fmax(mx[d][2], fabs(vel[d] + cs));
+  }
+}
+
+// Fold a wavefront's LF maxima into its slot (all lanes call; one atomic with
+// 3 DIM lanes on one line).
+template <int DIM>
+__device__ __forceinline__ void lf_commit_wave(LfSlot* slots, const double (&mx)[DIM][3]) {
+  const int lane = threadIdx.x & 63;
+  double v = 0.0;
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const double m = wave_max(mx[d][j]);
+      v = lane == 3 * d + j ? m : v;
+    }
+  }
+  const unsigned int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (lane < 3 * DIM)
+    atomicMax(&slots[wave % LF_SLOTS].bits[lane / 3][lane % 3], (unsigned long long)__double_as_longlong(v));
+}
+
+// The LF speeds of direction d over the slots (one whole wavefront; the same
+// values in every lane), as lf_bits holds them.
+template <int NV>
+__device__ __forceinline__ void lf_take_wave(const LfSlot* slots, int d, unsigned long long (&lf)[NV]) {
+  static_assert(LF_SLOTS <= 64, "one slot per lane");
+  const int lane = threadIdx.x & 63;
+  double m[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) m[j] = lane < LF_SLOTS ? __longlong_as_double((long long)slots[lane].bits[d][j]) : 0.0;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(wave_max(m[j]));
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (j == (k == 0 ? 0 : (k == NV - 1 ? 2 : 1))) lf[k] = b;
   }
 }
 
@@ -164,22 +239,10 @@ __global__ __launch_bounds__(RED_BLOCK) void lf_reduce_kernel(const double* __re
   for (int d = 0; d < DIM; ++d) mx[d][0] = mx[d][1] = mx[d][2] = 0.0;
   for (long long c = (long long)blockIdx.x * RED_BLOCK + threadIdx.x; c < ncell;
        c += (long long)gridDim.x * RED_BLOCK) {
-    const double rho = U[c], E = U[(NV - 1) * ncell + c];
-    const double ir = 1.0 / rho;
-    double vel[DIM], mu = 0.0;
+    double u[NV];
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-      vel[k] = U[(1 + k) * ncell + c] * ir;
-      mu += U[(1 + k) * ncell + c] * vel[k];
-    }
-    const double p = (gamma - 1.0) * (E - 0.5 * mu);
-    const double cs = sqrt(gamma * p * ir);
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      mx[d][0] = fmax(mx[d][0], fabs(vel[d] - cs));
-      mx[d][1] = fmax(mx[d][1], fabs(vel[d]));
-      mx[d][2] = fmax(mx[d][2], fabs(vel[d] + cs));
-    }
+    for (int v = 0; v < NV; ++v) u[v] = U[v * ncell + c];
+    lf_fold_cell<NV>(u, gamma, mx);
   }
   // the 3 DIM block maxima in one exchange through LDS
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;

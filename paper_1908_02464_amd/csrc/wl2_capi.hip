@@ -43,6 +43,7 @@ struct weno_l2is_ctx {
   double* ygh = nullptr;           // y state sides: ghost rows of both, [side][layer][nvar][nx]
   bool inflow_set = false;         // weno_l2is_set_inflow has been called
   double inflow_speed = 0.0;       // CFL speed sum_d(|u_d| + c), max over the inflow states
+  LfSlot* lfs = nullptr;           // 2D, LF splitting: three sets of LF slots (advance)
   StepCtl* ctl;
   KGrid g;
   KPhys ph;
@@ -156,6 +157,30 @@ bool inflow_missing(const weno_l2is_ctx* c) {
 
 int hip_err(hipError_t e) { return e == hipSuccess ? WL2_OK : WL2_E_HIP; }
 
+bool use_fused(const weno_l2is_ctx* c) { return c->dim == 3 && c->path != WL2_PATH_SWEEPS; }
+bool use_row(const weno_l2is_ctx* c) { return c->dim <= 2 && c->path != WL2_PATH_SWEEPS; }
+// 2D stages with the corrections in place (tile2d_kernel): every grid whose
+// faces all take the WENO flux, else grids below TILE_MAX_CELLS, where launches
+// and the chain of a stage set the time, not its work.  Measured us per step,
+// tile against row kernel and corrections (four quadrants, LLF): 64^2 31
+// against 52, 256^2 39 / 69, 512^2 71 / 109, 724^2 117 / 129, 1024^2 203 / 180;
+// every face WENO at 1024^2 644 / 1251.  A tuned rows-per-item or per-cell
+// corrections (WL2_PATH_FUSED_CELLS) ask for the row kernel.
+constexpr long long TILE_MAX_CELLS = 5ll << 17;
+bool use_tile(const weno_l2is_ctx* c) {
+  if (c->dim != 2 || c->zchunk > 0 || (c->path != WL2_PATH_AUTO && c->path != WL2_PATH_FUSED)) return false;
+  return c->p.hybrid == WL2_HYB_WENO_ONLY || c->ncell < TILE_MAX_CELLS;
+}
+
+// Rows per workgroup of the tile kernel: three (seven wavefronts, two
+// workgroups per CU), or one where that leaves at most three workgroups for
+// two CUs (the shortest chain: 128^2 34 us per step against 36, 256^2 46
+// against 39).
+int tile_rows(const weno_l2is_ctx* c) {
+  const long long wg = (long long)((c->n[0] + ROW_TILE - 1) / ROW_TILE) * c->n[1];
+  return 2 * wg <= 3 * (c->n_cu > 0 ? c->n_cu : 256) ? 1 : 3;
+}
+
 template <int NV, int DIR, int OUT>
 hipError_t launch_sweep_t(const weno_l2is_ctx* c, const SweepArgs& a) {
   const int n = c->n[DIR];
@@ -227,7 +252,7 @@ hipError_t launch_cfl(const weno_l2is_ctx* c, const double* U, double dt_fixed, 
 // over the slots into ctl->lf_bits (the slots are zero between reductions:
 // the control block starts zeroed and the finalize kernel clears them).
 // With y state sides the reduction's launch also fills their ghost rows for
-// stage time tc (as fill_yghosts).
+// stage time tc (as fill_yghosts; the tile kernel forms them itself).
 hipError_t launch_lf(const weno_l2is_ctx* c, const double* U, double tc) {
   const unsigned b = red_blocks(c->ncell);
   double* lo = const_cast<double*>(c->g.ygh[0]);
@@ -236,7 +261,7 @@ hipError_t launch_lf(const weno_l2is_ctx* c, const double* U, double tc) {
 #define WL2_LFR(NV, GH)                                                                      \
   hipLaunchKernelGGL((lf_reduce_kernel<NV, GH>), dim3(b), dim3(RED_BLOCK), 0, c->stream, U, \
                      c->ncell, c->gamma, c->ctl, c->g, tc, c->dx, r, lo, hi)
-  if (c->ygh) {
+  if (c->ygh && !use_tile(c)) {
     if (c->nvar != 4) return hipErrorInvalidValue;
     WL2_LFR(4, true);
   } else if (c->nvar == 3) {
@@ -251,8 +276,6 @@ hipError_t launch_lf(const weno_l2is_ctx* c, const double* U, double tc) {
   return hipGetLastError();
 }
 
-bool use_fused(const weno_l2is_ctx* c) { return c->dim == 3 && c->path != WL2_PATH_SWEEPS; }
-bool use_row(const weno_l2is_ctx* c) { return c->dim <= 2 && c->path != WL2_PATH_SWEEPS; }
 // advance() of a 1D grid keeps a step's stages on the chip (not with global
 // Lax-Friedrichs speeds, which need a grid-wide reduction per stage).
 bool use_line(const weno_l2is_ctx* c) {
@@ -315,9 +338,20 @@ struct ListTurn {
   }
 };
 
+// What a stage of an RK step does beside its own update.
+struct StageTurn {
+  bool fold_cfl = false;  // fold the CFL maximum of the output (next step's dt)
+  bool kclock = false;    // 1D/2D stage 1: the stage kernel forms the step's dt
+  bool commit = false;    // the stage after it: the tile kernel commits the clock
+  // tile kernel with LF splitting inside advance: index of the stage in the
+  // call (its speeds were folded by the stage before, from the second on), and
+  // whether a further one follows; -1: the speeds are reduced separately
+  int lf = -1;
+  bool lf_more = false;
+};
+
 hipError_t launch_row(const weno_l2is_ctx* c, int out_kind, const double* Uk, double* out,
-                      const double* Un, double ra, double rb, bool fold_cfl = false,
-                      bool kclock = false) {
+                      const double* Un, double ra, double rb, double tc, const StageTurn& t) {
   ListTurn turn(c);
   RowLaunch L;
   L.Uk = Uk;
@@ -336,8 +370,8 @@ hipError_t launch_row(const weno_l2is_ctx* c, int out_kind, const double* Uk, do
   L.list = c->list;
   L.list_n = turn.cur;
   L.list_clear = turn.next;
-  L.cfl = fold_cfl ? c->ctl : nullptr;
-  L.clock = kclock ? c->ctl : nullptr;
+  L.cfl = t.fold_cfl ? c->ctl : nullptr;
+  L.clock = t.kclock ? c->ctl : nullptr;
   L.cfl_dx = c->p.cfl * c->dx;
   L.s_floor = c->inflow_speed;
   L.fo_D = c->path == WL2_PATH_FUSED_CELLS ? nullptr : c->fo_D;
@@ -346,6 +380,19 @@ hipError_t launch_row(const weno_l2is_ctx* c, int out_kind, const double* Uk, do
   L.g = c->g;
   L.ph = c->ph;
   L.stream = c->stream;
+  L.commit = t.commit ? c->ctl : nullptr;
+  L.rule = nullptr;
+  L.dx = c->dx;
+  L.tc = tc;
+  L.lf_in = t.lf > 0 ? c->lfs + (t.lf % 3) * LF_SLOTS : nullptr;
+  L.lf_out = t.lf >= 0 && t.lf_more ? c->lfs + ((t.lf + 1) % 3) * LF_SLOTS : nullptr;
+  L.lf_clear = t.lf >= 0 ? c->lfs + ((t.lf + 2) % 3) * LF_SLOTS : nullptr;
+  if (use_tile(c)) {  // no list: the counters stay as they are
+    const YGhostRule rule = ghost_rule(c);
+    if (has_state_sides(&c->p, c->dim)) L.rule = &rule;
+    TimedLaunch tl(c, out_kind == OUT_RK ? "tile2d_rk" : "tile2d_rhs");
+    return tile2d_launch(L, tile_rows(c));
+  }
   hipError_t e = turn.reset ? row_reset(L) : hipSuccess;
   if (e != hipSuccess) return turn.done(e);
   {
@@ -437,10 +484,12 @@ hipError_t launch_fused(const weno_l2is_ctx* c, int out_kind, const double* Uk, 
 // dU/dt of the state Uk into out (WRITE then ACCUM over directions).
 hipError_t rhs_into(const weno_l2is_ctx* c, const double* Uk, double* out) {
   hipError_t e;
-  e = c->p.split == WL2_SPLIT_LF ? launch_lf(c, Uk, -1.0) : fill_yghosts(c, Uk, -1.0);
+  e = c->p.split == WL2_SPLIT_LF ? launch_lf(c, Uk, -1.0)
+      : use_tile(c)              ? hipSuccess
+                                 : fill_yghosts(c, Uk, -1.0);
   if (e != hipSuccess) return e;
   if (use_fused(c)) return launch_fused(c, OUT_WRITE, Uk, out, nullptr, 0.0, 1.0);
-  if (use_row(c)) return launch_row(c, OUT_WRITE, Uk, out, nullptr, 0.0, 1.0);
+  if (use_row(c)) return launch_row(c, OUT_WRITE, Uk, out, nullptr, 0.0, 1.0, -1.0, StageTurn());
   for (int d = 0; d < c->dim; ++d) {
     SweepArgs a{Uk, out, nullptr, nullptr, c->ctl, 0.0, 1.0};
     if ((e = launch_sweep(c, d, d == 0 ? OUT_WRITE : OUT_ACCUM, a)) != hipSuccess) return e;
@@ -448,20 +497,22 @@ hipError_t rhs_into(const weno_l2is_ctx* c, const double* Uk, double* out) {
   return hipSuccess;
 }
 
-// One RK stage: out = a Un + b (Uk + dt L(Uk)).  fold_cfl (fused 3D and row
-// 1D/2D paths): the stage kernels also fold the CFL maximum of `out` into
-// the control word.
-// kclock (1D/2D stage 1): the step's dt has not been formed yet; the stage
-// kernel forms it (finalize_dt_kernel's rule) and the clock still reads the
-// step's start, which the ghost rows take as their time (tc = 0).
+// One RK stage: out = a Un + b (Uk + dt L(Uk)), its ghosts at time t0 + tc dt.
+// kclock: the step's dt has not been formed yet; the stage kernel forms it
+// (finalize_dt_kernel's rule) and the clock still reads the step's start,
+// which the ghost rows take as their time (tc = 0).
 hipError_t stage(const weno_l2is_ctx* c, const double* Uk, const double* Un, double* out,
-                 double ra, double rb, double tc, bool fold_cfl = false, bool kclock = false) {
-  hipError_t e;
-  const double tg = kclock ? -1.0 : tc;  // -1: the clock's t
-  e = c->p.split == WL2_SPLIT_LF ? launch_lf(c, Uk, tg) : fill_yghosts(c, Uk, tg);
+                 double ra, double rb, double tc, const StageTurn& t) {
+  hipError_t e = hipSuccess;
+  const double tg = t.kclock ? -1.0 : tc;  // -1: the clock's t
+  if (c->p.split == WL2_SPLIT_LF) {
+    if (t.lf <= 0) e = launch_lf(c, Uk, tg);
+  } else if (!use_tile(c)) {
+    e = fill_yghosts(c, Uk, tg);
+  }
   if (e != hipSuccess) return e;
-  if (use_fused(c)) return launch_fused(c, OUT_RK, Uk, out, Un, ra, rb, fold_cfl);
-  if (use_row(c)) return launch_row(c, OUT_RK, Uk, out, Un, ra, rb, fold_cfl, kclock);
+  if (use_fused(c)) return launch_fused(c, OUT_RK, Uk, out, Un, ra, rb, t.fold_cfl);
+  if (use_row(c)) return launch_row(c, OUT_RK, Uk, out, Un, ra, rb, tg, t);
   for (int d = 0; d < c->dim - 1; ++d) {
     SweepArgs a{Uk, c->acc, nullptr, nullptr, c->ctl, 0.0, 1.0};
     if ((e = launch_sweep(c, d, d == 0 ? OUT_WRITE : OUT_ACCUM, a)) != hipSuccess) return e;
@@ -470,12 +521,23 @@ hipError_t stage(const weno_l2is_ctx* c, const double* Uk, const double* Un, dou
   return launch_sweep(c, c->dim - 1, OUT_RK, a);
 }
 
-hipError_t rk3(const weno_l2is_ctx* c, double* U, bool fold_cfl = false, bool kclock = false) {
+// One step; `step` of `n_steps` of an advance call (-1: a step by itself).
+hipError_t rk3(const weno_l2is_ctx* c, double* U, int step = -1, int n_steps = 0) {
+  const bool in_call = step >= 0, more = step + 1 < n_steps;
+  const bool lf = in_call && c->lfs != nullptr && c->p.split == WL2_SPLIT_LF && use_tile(c);
+  StageTurn t[3];
+  t[0].kclock = in_call && step > 0 && use_row(c);
+  t[1].commit = t[0].kclock;
+  t[2].fold_cfl = in_call && more && (use_fused(c) || use_row(c));
+  for (int k = 0; k < 3 && lf; ++k) {
+    t[k].lf = step > 0 ? 3 + k : k;  // the index mod 3, 0 only for the first stage
+    t[k].lf_more = more || k < 2;
+  }
   hipError_t e;
   // the stages at the times t0, t0 + dt, t0 + dt/2 of the Shu-Osher form
-  if ((e = stage(c, U, nullptr, c->U1, 0.0, 1.0, 0.0, false, kclock)) != hipSuccess) return e;
-  if ((e = stage(c, c->U1, U, c->U2, 0.75, 0.25, 1.0)) != hipSuccess) return e;
-  return stage(c, c->U2, U, U, 1.0 / 3.0, 2.0 / 3.0, 0.5, fold_cfl);
+  if ((e = stage(c, U, nullptr, c->U1, 0.0, 1.0, 0.0, t[0])) != hipSuccess) return e;
+  if ((e = stage(c, c->U1, U, c->U2, 0.75, 0.25, 1.0, t[1])) != hipSuccess) return e;
+  return stage(c, c->U2, U, U, 1.0 / 3.0, 2.0 / 3.0, 0.5, t[2]);
 }
 
 std::mutex g_cache_mu;
@@ -597,6 +659,8 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
     ok = hipMalloc(&c->fo3, sizeof(double) * fused3d_face_doubles(c->n)) == hipSuccess;
   if (ok && hyb3)
     ok = hipMalloc(&c->flist, sizeof(unsigned int) * fused3d_flist_entries(c->n)) == hipSuccess;
+  if (ok && c->dim == 2 && p->split == WL2_SPLIT_LF)
+    ok = hipMalloc(&c->lfs, 3 * LF_SLOTS * sizeof(LfSlot)) == hipSuccess;
   if (ok && c->dim == 1) ok = hipMalloc(&c->line, LINE_CTL_BYTES) == hipSuccess;
   if (ok && p->bc[0] == WL2_BC_INFLOW)
     ok = hipMalloc(&c->inflow, sizeof(double) * c->nvar * (size_t)ny * nz) == hipSuccess;
@@ -623,6 +687,7 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
     (void)hipFree(c->flist);
     (void)hipFree(c->counts);
     (void)hipFree(c->line);
+    (void)hipFree(c->lfs);
     (void)hipFree(c->inflow);
     (void)hipFree(c->ygh);
     (void)hipFree(c->ctl);
@@ -648,6 +713,7 @@ void weno_l2is_destroy(weno_l2is_ctx* c) {
   (void)hipFree(c->flist);
   (void)hipFree(c->counts);
   (void)hipFree(c->line);
+  (void)hipFree(c->lfs);
   (void)hipFree(c->inflow);
   (void)hipFree(c->ygh);
   (void)hipFree(c->ctl);
@@ -769,7 +835,8 @@ int weno_l2is_rhs_noalloc(const double* U, int nx, int ny, int nz, double dx, do
     off += align256(sizeof(unsigned int) * (2 * fused3d_count_entries(n) + 1));
   }
   c.list = (unsigned long long*)(base + off);
-  c.path = WL2_PATH_FUSED_CELLS;
+  // 2D: the tile kernel needs no list; else (and in 3D) per-cell corrections
+  c.path = dim == 2 ? WL2_PATH_AUTO : WL2_PATH_FUSED_CELLS;
   c.zchunk = 0;
   c.wpe = 2;
   c.list_par = 0;
@@ -819,7 +886,7 @@ int weno_l2is_advance(weno_l2is_ctx* c, double* U, int n_steps, double t_end) {
     return hip_err(line_advance(U, c->U1, c->line, c->ctl, c->p.cfl * c->dx, c->inflow_speed, n_steps, t_end,
                                 c->g, c->ph, c->stream));
   }
-  hipLaunchKernelGGL(set_t_end_kernel, dim3(1), dim3(64), 0, c->stream, c->ctl, t_end);
+  hipLaunchKernelGGL(set_t_end_kernel, dim3(1), dim3(64), 0, c->stream, c->ctl, t_end, c->lfs);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && use_line(c)) {
     TimedLaunch tl(c, "line_steps");
@@ -833,9 +900,8 @@ int weno_l2is_advance(weno_l2is_ctx* c, double* U, int n_steps, double t_end) {
   for (int s = 0; s < n_steps && e == hipSuccess; ++s) {
     // 1D/2D: from the second step the stage-1 kernel forms dt itself from
     // the folded maximum (one launch per step less)
-    const bool kclock = s > 0 && use_row(c);
-    if (!kclock) e = launch_cfl(c, U, 0.0, 1, fold && s > 0);
-    if (e == hipSuccess) e = rk3(c, U, fold && s + 1 < n_steps, kclock);
+    if (s == 0 || !use_row(c)) e = launch_cfl(c, U, 0.0, 1, fold && s > 0);
+    if (e == hipSuccess) e = rk3(c, U, s, n_steps);
   }
   return hip_err(e);
 }

@@ -100,6 +100,36 @@ struct StepCtl {
   LfSlot lf_slots[LF_SLOTS];     // global LF speeds being reduced (zero between reductions)
 };
 
+// Lane l's value from the lane a DPP control selects (lanes without a source
+// keep their own): two 32-bit moves in the VALU, where a shuffle goes through
+// the LDS unit and back.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp_move(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const int lo = (int)b, hi = (int)(b >> 32);
+  const unsigned int l = (unsigned int)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+  const unsigned int h = (unsigned int)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+  return __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
+}
+
+// The value of the next lane (lane 63 keeps its own).
+__device__ __forceinline__ double next_lane(double v) { return dpp_move<0x130>(v); }  // wave_shl:1
+
+// Maximum over the 64 lanes, in every lane (all lanes active): row shifts by
+// 1, 2, 4, 8, then the last lane of each row of 16 to the rows above it.
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, dpp_move<0x111>(v));
+  v = fmax(v, dpp_move<0x112>(v));
+  v = fmax(v, dpp_move<0x114>(v));
+  v = fmax(v, dpp_move<0x118>(v));
+  v = fmax(v, dpp_move<0x142, 0xa>(v));
+  v = fmax(v, dpp_move<0x143, 0xc>(v));
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)b, 63);
+  const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Fold a maximum (> 0, or +inf standing for NaN) into the wave's slot.
 __device__ __forceinline__ void cfl_fold(StepCtl* ctl, double m) {
   const unsigned wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -130,13 +160,8 @@ __device__ __forceinline__ double cfl_take(StepCtl* ctl) {
 __device__ __forceinline__ double cfl_peek_wave(const StepCtl* ctl) {
   static_assert(CFL_SLOTS <= 64, "one slot per lane");
   const int lane = threadIdx.x & 63;
-  unsigned long long m = lane < CFL_SLOTS ? ctl->smax[lane].bits : 0ull;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long q = __shfl_xor(m, o, 64);
-    m = q > m ? q : m;
-  }
-  return __longlong_as_double((long long)m);
+  // the folded values are >= 0 (a NaN was raised to +inf)
+  return wave_max(lane < CFL_SLOTS ? __longlong_as_double((long long)ctl->smax[lane].bits) : 0.0);
 }
 
 // cfl_take by one whole wavefront (lane s reads and clears slot s): one
@@ -228,36 +253,6 @@ __device__ __forceinline__ double cfl_speed_u(const double (&u)[NV], double gamm
 
 // Running maximum that lets a NaN win.
 __device__ __forceinline__ double nan_max(double acc, double s) { return (s != s || s > acc) ? s : acc; }
-
-// Lane l's value from the lane a DPP control selects (lanes without a source
-// keep their own): two 32-bit moves in the VALU, where a shuffle goes through
-// the LDS unit and back.
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ double dpp_move(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const int lo = (int)b, hi = (int)(b >> 32);
-  const unsigned int l = (unsigned int)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
-  const unsigned int h = (unsigned int)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
-}
-
-// The value of the next lane (lane 63 keeps its own).
-__device__ __forceinline__ double next_lane(double v) { return dpp_move<0x130>(v); }  // wave_shl:1
-
-// Maximum over the 64 lanes, in every lane (all lanes active): row shifts by
-// 1, 2, 4, 8, then the last lane of each row of 16 to the rows above it.
-__device__ __forceinline__ double wave_max(double v) {
-  v = fmax(v, dpp_move<0x111>(v));
-  v = fmax(v, dpp_move<0x112>(v));
-  v = fmax(v, dpp_move<0x114>(v));
-  v = fmax(v, dpp_move<0x118>(v));
-  v = fmax(v, dpp_move<0x142, 0xa>(v));
-  v = fmax(v, dpp_move<0x143, 0xc>(v));
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)b, 63);
-  const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(b >> 32), 63);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 // Fold one wave's CFL maximum and non-physical flag into the step control
 // word (one atomic per wave; a NaN maximum is raised to +inf so that it

@@ -13,11 +13,8 @@
 //    stages on a range that shrinks by three cells per side and stage; only
 //    the first and the last state touch memory.  The halo cells are computed
 //    by both neighbours from the same values, so with the same bits.
-// A flagged face is corrected where it is found: the (face, flagged field)
-// pairs of a wavefront are spread over its lanes, so that a wavefront with up
-// to 64 pairs forms one field's WENO flux per lane (a lane per face would form
-// every field that some lane flags, one after the other).  The arithmetic of a
-// face, of its correction and of a cell's update is that of the stage kernels
+// A flagged face is corrected where it is found (wave_face).  The arithmetic of
+// a face, of its correction and of a cell's update is that of the stage kernels
 // (row_item, row_fix_kernel), operation for operation: the same bits.
 // Measured, us per step (before: stage and correction launches, and up to
 // 1024 cells one workgroup through global memory): Riemann problem 200 cells
@@ -25,117 +22,13 @@
 // cells 40 -> 17 and 400000 cells 360 -> 86.
 #pragma once
 #include "wl2_aux.hpp"
-#include "wl2_lface.hpp"
 #include "wl2_row_launch.hpp"
+#include "wl2_wface.hpp"
 
 namespace wl2 {
 
 constexpr int LNV = 3;
 constexpr int LW = 63;  // cells of a wavefront's 64 faces
-
-// Orders the LDS accesses of one wavefront (its lanes exchange values): the
-// LDS unit takes them in issue order, the compiler must not reorder them.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Stencil of the face whose cell j - 2 is at position p of the record planes
-// [6][P] (U, p, c, 1/sqrt(rho)).
-template <int P>
-struct LineSrc {
-  const double* rec;
-  int p;
-  __device__ __forceinline__ void get(int m, LRec<LNV>& r) const {
-    const double* q = rec + p + m;
-#pragma unroll
-    for (int v = 0; v < LNV; ++v) r.U[v] = q[v * P];
-    r.p = q[LNV * P];
-    r.c = q[(LNV + 1) * P];
-    r.iw = q[(LNV + 2) * P];
-  }
-};
-
-template <int P>
-__device__ __forceinline__ void line_put(double* rec, int p, const LRec<LNV>& r) {
-  double* q = rec + p;
-#pragma unroll
-  for (int v = 0; v < LNV; ++v) q[v * P] = r.U[v];
-  q[LNV * P] = r.p;
-  q[(LNV + 1) * P] = r.c;
-  q[(LNV + 2) * P] = r.iw;
-}
-
-// Per-wavefront scratch of the corrections: what a lane needs to form field k
-// of the face of another lane, and the list of (field << 6 | lane) pairs.
-struct LineScratch {
-  double u[64], b1[64], b2[64], ic[64], irho[64];
-  double a[LNV][64];   // splitting speeds; then the field's WENO flux
-  double dv[LNV][64];
-  unsigned char pair[LNV * 64];
-};
-
-// Linear flux (times 60) of the face left of this lane's cell, and its
-// correction dF if its detector asks for it (returned).  The face of lane l
-// has its cell j - 2 at position p0 + l.  Called by whole wavefronts; lanes
-// without a face pass active = false.
-template <int P, int SPLIT, int HYB, int W>
-__device__ __forceinline__ bool line_face(const double* rec, int p0, bool active, const KPhys& ph,
-                                          LineScratch& sc, double (&F60)[LNV], double (&dF)[LNV]) {
-  const int lane = threadIdx.x & 63;
-  FaceState<LNV> st;
-  unsigned mask = face_linear_st<LNV, 0, SPLIT, HYB, false>(LineSrc<P>{rec, p0 + lane}, ph,
-                                                            ph.eps_thr[0], nullptr, F60, st);
-  if (!active) mask = 0u;
-#pragma unroll
-  for (int v = 0; v < LNV; ++v) dF[v] = 0.0;
-  const unsigned long long b0 = __ballot(mask & 1u), b1 = __ballot(mask & 2u), b2 = __ballot(mask & 4u);
-  if ((b0 | b1 | b2) == 0ull) return false;
-  if (mask) {
-    const unsigned long long below = (1ull << lane) - 1ull;
-    const int n0 = __popcll(b0), n1 = __popcll(b1);
-    if (mask & 1u) sc.pair[__popcll(b0 & below)] = (unsigned char)lane;
-    if (mask & 2u) sc.pair[n0 + __popcll(b1 & below)] = (unsigned char)(64 | lane);
-    if (mask & 4u) sc.pair[n0 + n1 + __popcll(b2 & below)] = (unsigned char)(128 | lane);
-    sc.u[lane] = st.s.u[0];
-    sc.b1[lane] = st.s.b1;
-    sc.b2[lane] = st.s.b2;
-    sc.ic[lane] = st.s.ic;
-    sc.irho[lane] = st.s.irho;
-#pragma unroll
-    for (int k = 0; k < LNV; ++k) {
-      sc.a[k][lane] = st.a[k];
-      sc.dv[k][lane] = st.dv[k];
-    }
-  }
-  wave_lds_fence();
-  const int total = __popcll(b0) + __popcll(b1) + __popcll(b2);
-  for (int i = lane; i < total; i += 64) {
-    const int e = sc.pair[i], fl = e & 63, k = e >> 6;
-    Roe<LNV> s;
-    s.u[0] = sc.u[fl];
-    s.b1 = sc.b1[fl];
-    s.b2 = sc.b2[fl];
-    s.ic = sc.ic[fl];
-    s.irho = sc.irho[fl];
-    double r[LNV];
-    left_row_rt<LNV, 0>(s, k, r);
-    sc.a[k][fl] = lean_field_row<LNV, 0, W, -1>(LineSrc<P>{rec, p0 + fl}, r, s, sc.a[k][fl], sc.dv[k][fl], ph);
-  }
-  wave_lds_fence();
-  if (mask) {
-    double LF[LNV], f[LNV];
-    project<LNV, 0>(st.s, st.Fc6, LF);
-#pragma unroll
-    for (int k = 0; k < LNV; ++k) f[k] = ((mask >> k) & 1u) ? sc.a[k][lane] : LF[k] + st.a[k] * st.dv[k];
-    back_project<LNV, 0>(st.s, f, dF);
-#pragma unroll
-    for (int v = 0; v < LNV; ++v) dF[v] -= F60[v] * (1.0 / 60.0);
-  }
-  wave_lds_fence();  // the scratch is free for the wavefront's next faces
-  return mask != 0u;
-}
 
 // Stage update of one cell from its two faces (row_item's and
 // row_fix_kernel's operations): u becomes the stage's result.
@@ -182,7 +75,8 @@ __global__ __launch_bounds__(NW * 64) void line_steps_kernel(LineStepsArgs s, KG
   constexpr int NC = NW * LW;  // cells at most
   constexpr int P = NC + 8;          // positions k + 3 of the cells k = -3 .. n + 2, faces up to NC
   __shared__ double rec[2][(LNV + 3) * P];
-  __shared__ LineScratch scr[NW];
+  __shared__ FaceScratch<LNV> scr[NW];
+  __shared__ double roe[NW][LNV][64];
   __shared__ double red[NW];
   __shared__ unsigned int redbad[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -209,12 +103,12 @@ __global__ __launch_bounds__(NW * 64) void line_steps_kernel(LineStepsArgs s, KG
     if (!own) return;
     LRec<LNV> r;
     make_lrec<LNV>(u, ph, r);
-    line_put<P>(to, j + 3, r);
+    lane_put<LNV, P>(to + j + 3, r);
     for (unsigned int m = gh; (m & 0x3fu) != 0u; m &= m - 1u) {
       const int q = __builtin_ctz(m);
       LRec<LNV> gr = r;
       if ((gh >> (8 + q)) & 1u) gr.U[1] = -gr.U[1];
-      line_put<P>(to, q < 3 ? q : n + q, gr);
+      lane_put<LNV, P>(to + (q < 3 ? q : n + q), gr);
     }
   };
   auto fold_cfl = [&]() {  // CFL maximum of u, met in LDS at the next barrier
@@ -256,7 +150,7 @@ __global__ __launch_bounds__(NW * 64) void line_steps_kernel(LineStepsArgs s, KG
       line_rk(st, ra, rb);
       if (f0 < n) {  // uniform in the wavefront: it owns a cell
         double F60[LNV], dF[LNV], Fr[LNV], dr[LNV];
-        const bool m = line_face<P, SPLIT, HYB, W>(rec[cur], f0, j <= n, ph, scr[wave], F60, dF);
+        const bool m = wave_face<LNV, 0, P, SPLIT, HYB, W>(rec[cur] + f0, 1, j <= n, ph, nullptr, scr[wave], roe[wave], F60, dF);
         const unsigned long long mw = __ballot(m);
 #pragma unroll
         for (int v = 0; v < LNV; ++v) {
@@ -334,7 +228,8 @@ __device__ __forceinline__ void line_fold(LineCtl::Slot* set, double smax, bool 
 template <int SPLIT, int HYB, int W>
 __global__ __launch_bounds__(64) void line_step_kernel(LineStepArgs a, KGrid g, KPhys ph) {
   __shared__ double rec[(LNV + 3) * LP];
-  __shared__ LineScratch scr;
+  __shared__ FaceScratch<LNV> scr;
+  __shared__ double roe[LNV][64];
   const int lane = threadIdx.x, n = g.n[0];
   const int x0 = blockIdx.x * LT, k = x0 - LHALO + lane;
   const bool per = g.bc_lo[0] == BC_PERIODIC;
@@ -407,18 +302,18 @@ __global__ __launch_bounds__(64) void line_step_kernel(LineStepArgs a, KGrid g, 
     line_rk(st, ra, rb);
     LRec<LNV> r;
     make_lrec<LNV>(u, ph, r);
-    line_put<LP>(rec, lane + 3, r);
+    lane_put<LNV, LP>(rec + lane + 3, r);
     wave_lds_fence();
     if (ghost && !inflow) {
-      LineSrc<LP>{rec, src + 3}.get(0, r);
+      LaneSrc<LNV, LP>{rec + src + 3, 1}.get(0, r);
       if (flip) r.U[1] = -r.U[1];
-      line_put<LP>(rec, lane + 3, r);
+      lane_put<LNV, LP>(rec + lane + 3, r);
     }
     wave_lds_fence();
     const int lo = 3 * (st + 1), hi = 64 - lo;  // cells updated by this stage
     double F60[LNV], dF[LNV], Fr[LNV], dr[LNV];
     const bool face = lane >= lo && lane <= hi && (per || (k >= 0 && k <= n));
-    const bool m = line_face<LP, SPLIT, HYB, W>(rec, 0, face, ph, scr, F60, dF);
+    const bool m = wave_face<LNV, 0, LP, SPLIT, HYB, W>(rec, 1, face, ph, nullptr, scr, roe, F60, dF);
     const unsigned long long mw = __ballot(m);
     const bool mr = ((mw >> lane) & 2ull) != 0ull;
 #pragma unroll

@@ -9,6 +9,8 @@ namespace wl2 {
 constexpr int ROW_TILE = 63;     // columns per work item (one wavefront)
 constexpr int ROW_MAX_YCH = 62;  // rows per work item (flag bits per row)
 
+struct YGhostRule;
+
 struct RowLaunch {
   const double* Uk;
   double* out;
@@ -28,6 +30,13 @@ struct RowLaunch {
   StepCtl* clock;            // RK stage 1: the stage kernel forms the step's dt
                              // from the CFL maximum folded here (or null)
   double cfl_dx, s_floor;    // with clock: CFL number x dx, inflow speed floor
+  // tile kernel only
+  StepCtl* commit;           // stage 2: commit the clock that stage 1 formed (or null)
+  const YGhostRule* rule;    // state ghosts of the y sides (or null: none)
+  double dx, tc;             // with them: cell size and stage time (yghost_time)
+  const LfSlot* lf_in;       // LF splitting: speeds of the input (null: ctl->lf_bits),
+  LfSlot* lf_out;            // where the output's are folded (or null),
+  LfSlot* lf_clear;          // and the set to clear for the next stage (or null)
   // face-once corrections (2D, long lists): per-entry face changes
   // [2][nvar][fo_cap] and the cell -> entry map [ncell]; null: per cell
   double* fo_D;
@@ -45,6 +54,10 @@ struct RowLaunch {
 hipError_t row_reset(const RowLaunch& L);
 hipError_t row_launch(const RowLaunch& L);
 hipError_t row_fix(const RowLaunch& L);
+
+// 2D: one stage with its corrections in one launch, `rows` (1 or 3) rows per
+// workgroup (list and face-once members unused).
+hipError_t tile2d_launch(const RowLaunch& L, int rows);
 
 // 1D grids: n_steps clock steps of U (SSP-RK3, device CFL dt, the clock rule
 // of finalize_dt_kernel; not with global LF splitting, whose speeds need a
