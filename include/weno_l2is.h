@@ -278,17 +278,16 @@ void weno_l2is_destroy(weno_l2is_ctx *ctx);
  * Batched and served form: many independent 1D/2D runs of uneven sizes
  * advanced together.  Each step is one replay of a captured hipGraph whose
  * persistent kernels walk tables of work items over all admitted runs (an
- * item is 63 columns x a chunk of rows of one run: the unit of the
- * single-grid 1D/2D stage kernel); every run keeps its own CFL dt, clock
+ * item is a tile of one run: 63 columns x three rows in 2D, 46 cells in 1D,
+ * the units of the single-grid tile and line kernels); every run keeps its own CFL dt, clock
  * (stopping exactly at its t_end, or at a non-physical state) and status.  A
  * run's result is bit-identical to running it alone through
  * weno_l2is_advance (same device code, same operation order).
  * The engine allocates `hbm_budget_bytes` once at creation and sub-allocates
  * runs from it: admission fails with WL2_E_BUDGET when a run's footprint
  * (3 state arrays) does not fit or all `max_slots` slots are taken.  Beside
- * the budget it holds a correction list of budget/72 entries of 8 bytes (one
- * per admissible cell), the slot table and the work tables (which grow, with
- * a new graph, when the admitted runs need more items than ever before).
+ * the budget it holds the slot table and the work tables (which grow, with a
+ * new graph, when the admitted runs need more items than ever before).
  * LF splitting (WL2_SPLIT_LF) and 3D grids are not supported in a batch
  * (WL2_E_PARAM / WL2_E_SHAPE).
  * All calls are asynchronous on the engine's stream unless noted.
@@ -327,8 +326,8 @@ int weno_l2is_batch_fetch(weno_l2is_batch *b, int slot, double *U_out,
                           unsigned *steps);
 
 /* Launch shape of the batched stage kernels: `rows` rows per work item of a
- * 2D run (1..62; a work item is 63 columns of one run, one wavefront) and
- * `blocks` workgroups in the persistent grid (64..65536); 0 keeps the
+ * 2D run (1..62: below three one row, else three, the two builds of the tile
+ * kernel) and `blocks` workgroups in the persistent grid (64..65536); 0 keeps the
  * current value.  Results do not depend on either (every face is computed by
  * the same arithmetic), only the speed does.  Returns WL2_E_PARAM for values
  * outside these ranges. */

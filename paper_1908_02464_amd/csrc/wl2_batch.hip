@@ -22,7 +22,7 @@ namespace {
 
 constexpr size_t ALIGN = 256;
 constexpr int ROW_BLOCKS_DEFAULT = 2048;  // persistent grid of the row kernels
-constexpr int ROWS_DEFAULT = 4;           // rows per work item of a 2D run
+constexpr int ROWS_DEFAULT = 4;           // rows asked for per work item of a 2D run
 constexpr int RED_BLOCKS = 1024;
 
 struct SlotInfo {
@@ -30,9 +30,14 @@ struct SlotInfo {
   bool reported = false;
   int n[3] = {1, 1, 1};
   int dim = 1, nvar = 3;
+  bool other = false;  // not the default scheme (LLF splitting, per-field switch, Eq.(28))
   long long ncell = 0;
   size_t off = 0, bytes = 0;
 };
+
+// Rows of a 2D work item: the tile kernel has builds for three rows and for
+// one (below three asked for).
+int tile_rows(int rows) { return rows < 3 ? 1 : 3; }
 
 size_t round_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -52,8 +57,8 @@ struct weno_l2is_batch {
   BGrid* h_grids = nullptr;
   StepCtl* d_ctl = nullptr;
   StepCtl* h_ctl = nullptr;  // staging for admission
-  RowItem* d_items[2] = {nullptr, nullptr};  // work items of the 1D / 2D runs
-  RowItem* h_items[2] = {nullptr, nullptr};
+  BatchItem* d_items[2] = {nullptr, nullptr};  // work items of the 1D / 2D runs
+  BatchItem* h_items[2] = {nullptr, nullptr};
   int item_cap[2] = {0, 0};
   int chunk_cap = 0;
   int* d_cslot = nullptr;
@@ -63,8 +68,6 @@ struct weno_l2is_batch {
   long long* h_cfirst = nullptr;
   int* h_ccount = nullptr;
   int* d_counts = nullptr;  // [0] chunks, [1] active slots, [2] 1D items, [3] 2D items
-  unsigned long long* d_list = nullptr;  // cells listed for the nonlinear correction
-  unsigned int* d_list_n = nullptr;
   int* h_counts = nullptr;
   int* d_slotlist = nullptr;
   int* h_slotlist = nullptr;
@@ -76,6 +79,7 @@ struct weno_l2is_batch {
   bool dirty = true;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
+  bool graph_fast = true;  // the captured graph's stage kernels: the default scheme only
   int rows = ROWS_DEFAULT;
   int row_blocks = ROW_BLOCKS_DEFAULT;
 };
@@ -136,9 +140,9 @@ hipError_t reserve_items(weno_l2is_batch* b, int d, long long n) {
   hipError_t e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) return e;
   b->upload_pending = false;
-  RowItem *dn = nullptr, *hn = nullptr;
-  if ((e = hipMalloc(&dn, sizeof(RowItem) * (size_t)cap)) != hipSuccess) return e;
-  if ((e = hipHostMalloc(&hn, sizeof(RowItem) * (size_t)cap, 0)) != hipSuccess) {
+  BatchItem *dn = nullptr, *hn = nullptr;
+  if ((e = hipMalloc(&dn, sizeof(BatchItem) * (size_t)cap)) != hipSuccess) return e;
+  if ((e = hipHostMalloc(&hn, sizeof(BatchItem) * (size_t)cap, 0)) != hipSuccess) {
     (void)hipFree(dn);
     return e;
   }
@@ -154,30 +158,30 @@ hipError_t reserve_items(weno_l2is_batch* b, int d, long long n) {
 hipError_t upload_tables(weno_l2is_batch* b) {
   hipError_t e = wait_upload(b);
   if (e != hipSuccess) return e;
+  const int rows = tile_rows(b->rows);
   // sizes first (a buffer may have to grow)
   long long need[2] = {0, 0};
   for (int s = 0; s < b->max_slots; ++s) {
     const SlotInfo& si = b->slots[s];
     if (!si.used) continue;
-    const long long tiles = (si.n[0] + ROW_TILE - 1) / ROW_TILE;
-    if (si.dim == 1) need[0] += tiles;
-    else need[1] += tiles * ((si.n[1] + b->rows - 1) / b->rows);
+    if (si.dim == 1) need[0] += (si.n[0] + LT - 1) / LT;
+    else need[1] += (long long)((si.n[0] + RT - 1) / RT) * ((si.n[1] + rows - 1) / rows);
   }
   for (int d = 0; d < 2; ++d)
     if ((e = reserve_items(b, d, need[d] > 0 ? need[d] : 1)) != hipSuccess) return e;
   int ni[2] = {0, 0};
   int nch = 0, nact = 0;
+  bool fast = true;
   for (int s = 0; s < b->max_slots; ++s) {
     const SlotInfo& si = b->slots[s];
     if (!si.used) continue;
     b->h_slotlist[nact++] = s;
-    for (int x0 = 0; x0 < si.n[0]; x0 += ROW_TILE) {
-      if (si.dim == 1) {
-        b->h_items[0][ni[0]++] = RowItem{s, x0, 0, 1};
-      } else {
-        for (int y0 = 0; y0 < si.n[1]; y0 += b->rows)
-          b->h_items[1][ni[1]++] = RowItem{s, x0, y0, std::min(y0 + b->rows, si.n[1])};
-      }
+    if (si.other) fast = false;
+    if (si.dim == 1) {
+      for (int x0 = 0; x0 < si.n[0]; x0 += LT) b->h_items[0][ni[0]++] = BatchItem{s, x0, 0, 0};
+    } else {
+      for (int x0 = 0; x0 < si.n[0]; x0 += RT)
+        for (int y0 = 0; y0 < si.n[1]; y0 += rows) b->h_items[1][ni[1]++] = BatchItem{s, x0, y0, 0};
     }
     for (long long c0 = 0; c0 < si.ncell; c0 += BATCH_CHUNK) {
       if (nch >= b->chunk_cap) return hipErrorOutOfMemory;
@@ -187,6 +191,10 @@ hipError_t upload_tables(weno_l2is_batch* b) {
       ++nch;
     }
   }
+  if (fast != b->graph_fast) {
+    b->graph_fast = fast;
+    drop_graph(b);  // the other build of the stage kernels
+  }
   b->h_counts[0] = nch;
   b->h_counts[1] = nact;
   b->h_counts[2] = ni[0];
@@ -194,7 +202,7 @@ hipError_t upload_tables(weno_l2is_batch* b) {
   hipStream_t st = b->stream;
   for (int d = 0; d < 2; ++d)
     if (ni[d] > 0 &&
-        (e = hipMemcpyAsync(b->d_items[d], b->h_items[d], sizeof(RowItem) * ni[d], hipMemcpyHostToDevice, st)))
+        (e = hipMemcpyAsync(b->d_items[d], b->h_items[d], sizeof(BatchItem) * ni[d], hipMemcpyHostToDevice, st)))
       return e;
   if ((e = hipMemcpyAsync(b->d_cslot, b->h_cslot, sizeof(int) * nch, hipMemcpyHostToDevice, st)) ||
       (e = hipMemcpyAsync(b->d_cfirst, b->h_cfirst, sizeof(long long) * nch, hipMemcpyHostToDevice, st)) ||
@@ -213,19 +221,26 @@ hipError_t upload_tables(weno_l2is_batch* b) {
 hipError_t enqueue_step(weno_l2is_batch* b) {
   hipStream_t st = b->stream;
   BChunks ch{0, 0, b->d_cslot, b->d_cfirst, b->d_ccount};
-  hipLaunchKernelGGL(batch_cfl_kernel, dim3(RED_BLOCKS), dim3(RED_BLOCK), 0, st, b->d_grids, ch,
-                     b->d_counts + 0);
-  hipLaunchKernelGGL(batch_finalize_kernel, dim3(16), dim3(256), 0, st, b->d_grids, b->d_slotlist,
-                     b->d_counts + 1);
-  for (int stage = 0; stage < 3; ++stage) {
-    hipLaunchKernelGGL(row_list_reset_kernel, dim3(1), dim3(64), 0, st, b->d_list_n);
-    hipLaunchKernelGGL(batch_row_kernel<3>, dim3(b->row_blocks), dim3(RW), 0, st, b->d_grids,
-                       b->d_items[0], b->d_counts + 2, stage, b->d_list, b->d_list_n);
-    hipLaunchKernelGGL(batch_row_kernel<4>, dim3(b->row_blocks), dim3(RW), 0, st, b->d_grids,
-                       b->d_items[1], b->d_counts + 3, stage, b->d_list, b->d_list_n);
-    hipLaunchKernelGGL(batch_fix_kernel, dim3(1024), dim3(128), 0, st, b->d_grids, b->d_list,
-                       b->d_list_n, stage);
-  }
+  hipLaunchKernelGGL(batch_cfl_kernel, dim3(RED_BLOCKS), dim3(RED_BLOCK), 0, st, b->d_grids,
+                     (const double*)b->pool, b->d_ctl, ch, b->d_counts + 0);
+  hipLaunchKernelGGL(batch_finalize_kernel, dim3(std::min(b->max_slots, 1024)), dim3(64), 0, st, b->d_grids,
+                     b->d_ctl, b->d_slotlist, b->d_counts + 1);
+#define WL2_BATCH_STAGE(R, S, F)                                                                     \
+  hipLaunchKernelGGL((batch_stage_kernel<R, S, F>), dim3(b->row_blocks), dim3((2 * R + 1) * 64), 0, st, \
+                     b->d_grids, (double*)b->pool, b->d_ctl, b->d_items[0], b->d_items[1], b->d_counts + 2)
+#define WL2_BATCH_STAGES(R, F) \
+  do {                         \
+    WL2_BATCH_STAGE(R, 0, F);  \
+    WL2_BATCH_STAGE(R, 1, F);  \
+    WL2_BATCH_STAGE(R, 2, F);  \
+  } while (0)
+  const bool one = tile_rows(b->rows) == 1;
+  if (one && b->graph_fast) WL2_BATCH_STAGES(1, true);
+  else if (one) WL2_BATCH_STAGES(1, false);
+  else if (b->graph_fast) WL2_BATCH_STAGES(3, true);
+  else WL2_BATCH_STAGES(3, false);
+#undef WL2_BATCH_STAGE
+#undef WL2_BATCH_STAGES
   return hipGetLastError();
 }
 
@@ -271,11 +286,7 @@ int weno_l2is_batch_create(size_t hbm_budget_bytes, int max_slots, void* hip_str
   b->slots.resize(max_slots);
   // every chunk covers at least one 3-variable cell of 3 arrays (72 bytes)
   b->chunk_cap = (int)std::min<size_t>((size_t)1 << 26, b->budget / (72 * BATCH_CHUNK) + max_slots + 16);
-  // a list entry per admissible cell (at least 72 bytes of state each)
-  const size_t list_cap = b->budget / 72 + 1;
   bool ok = hipMalloc(&b->pool, b->budget) == hipSuccess &&
-            hipMalloc(&b->d_list, sizeof(unsigned long long) * list_cap) == hipSuccess &&
-            hipMalloc(&b->d_list_n, sizeof(unsigned int)) == hipSuccess &&
             hipMalloc(&b->d_grids, sizeof(BGrid) * max_slots) == hipSuccess &&
             hipMalloc(&b->d_ctl, sizeof(StepCtl) * max_slots) == hipSuccess &&
             hipMalloc(&b->d_cslot, sizeof(int) * b->chunk_cap) == hipSuccess &&
@@ -338,6 +349,7 @@ int weno_l2is_batch_admit(weno_l2is_batch* b, int nx, int ny, int nz, double dx,
   si.dim = grid_dim(ny, nz);
   si.nvar = si.dim + 2;
   si.ncell = (long long)nx * ny;
+  si.other = p->split != WL2_SPLIT_LLF || p->hybrid != WL2_HYB_PER_FIELD || p->weights != WL2_W_L2IS;
   const size_t arr = round_up(sizeof(double) * (size_t)si.nvar * si.ncell);
   si.bytes = arr * 3;
   if (!pool_alloc(b, si.bytes, &si.off)) return WL2_E_BUDGET;
@@ -349,11 +361,10 @@ int weno_l2is_batch_admit(weno_l2is_batch* b, int nx, int ny, int nz, double dx,
   BGrid& G = b->h_grids[s];
   std::memset(&G, 0, sizeof(G));
   fill_grid_desc(si.n, si.dim, dx, gamma, *p, G.g, G.ph);
-  char* base = b->pool + si.off;
-  G.U = (double*)base;
-  G.U1 = (double*)(base + arr);
-  G.U2 = (double*)(base + 2 * arr);
-  G.ctl = b->d_ctl + s;
+  G.U = (long long)(si.off / sizeof(double));
+  G.U1 = (long long)((si.off + arr) / sizeof(double));
+  G.U2 = (long long)((si.off + 2 * arr) / sizeof(double));
+  double* const dU = (double*)(b->pool + si.off);
   G.cfl_dx = p->cfl * dx;
   G.dim = si.dim;
   G.nv = si.nvar;
@@ -364,7 +375,7 @@ int weno_l2is_batch_admit(weno_l2is_batch* b, int nx, int ny, int nz, double dx,
   C.t_end = t_end;
   const size_t ubytes = sizeof(double) * (size_t)si.nvar * si.ncell;
   hipStream_t st = b->stream;
-  if ((e = hipMemcpyAsync(G.U, U0, ubytes, u0_on_host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st)) ||
+  if ((e = hipMemcpyAsync(dU, U0, ubytes, u0_on_host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st)) ||
       (e = hipMemcpyAsync(b->d_grids + s, &G, sizeof(BGrid), hipMemcpyHostToDevice, st)) ||
       (e = hipMemcpyAsync(b->d_ctl + s, &C, sizeof(StepCtl), hipMemcpyHostToDevice, st)) ||
       (e = hipEventRecord(b->ev_upload, st))) {
@@ -397,7 +408,7 @@ int weno_l2is_batch_advance(weno_l2is_batch* b, int n_steps) {
   if ((e = ensure_graph(b)) != hipSuccess) return herr(e);
   for (int k = 0; k < n_steps; ++k)
     if ((e = hipGraphLaunch(b->gexec, b->stream)) != hipSuccess) return herr(e);
-  hipLaunchKernelGGL(batch_gather_kernel, dim3(4), dim3(256), 0, b->stream, b->d_grids,
+  hipLaunchKernelGGL(batch_gather_kernel, dim3(4), dim3(256), 0, b->stream, b->d_ctl,
                      b->d_slotlist, b->d_counts + 1, b->d_state);
   if ((e = hipGetLastError()) != hipSuccess) return herr(e);
   if ((e = hipMemcpyAsync(b->h_state, b->d_state, sizeof(SlotState) * b->state_n,
@@ -435,11 +446,10 @@ int weno_l2is_batch_fetch(weno_l2is_batch* b, int slot, double* U_out, int out_o
   if (!b || !U_out) return WL2_E_NULL;
   if (slot < 0 || slot >= b->max_slots || !b->slots[slot].used) return WL2_E_SLOT;
   SlotInfo& si = b->slots[slot];
-  const BGrid& G = b->h_grids[slot];
   StepCtl C;
   const size_t ubytes = sizeof(double) * (size_t)si.nvar * si.ncell;
   hipError_t e;
-  if ((e = hipMemcpyAsync(U_out, G.U, ubytes, out_on_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice,
+  if ((e = hipMemcpyAsync(U_out, b->pool + si.off, ubytes, out_on_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice,
                           b->stream)) ||
       (e = hipMemcpyAsync(&C, b->d_ctl + slot, sizeof(C), hipMemcpyDeviceToHost, b->stream)) ||
       (e = hipStreamSynchronize(b->stream)))
@@ -464,6 +474,7 @@ int weno_l2is_batch_tune(weno_l2is_batch* b, int rows, int blocks) {
   if (rows && rows != b->rows) {
     b->rows = rows;
     b->dirty = true;  // the 2D items follow the rows per item
+    drop_graph(b);    // and so does the build of the stage kernels
   }
   if (blocks && blocks != b->row_blocks) {
     b->row_blocks = blocks;
@@ -487,8 +498,6 @@ void weno_l2is_batch_destroy(weno_l2is_batch* b) {
   if (b->ev_state) (void)hipEventDestroy(b->ev_state);
   if (b->ev_upload) (void)hipEventDestroy(b->ev_upload);
   (void)hipFree(b->pool);
-  (void)hipFree(b->d_list);
-  (void)hipFree(b->d_list_n);
   (void)hipFree(b->d_grids);
   (void)hipFree(b->d_ctl);
   for (int d = 0; d < 2; ++d) {

@@ -1,25 +1,29 @@
 // Batched form: many independent 1D/2D grids advanced by persistent kernels
 // walking tables of work items (one table per dimension), so a fixed launch
 // shape serves any mix of grid sizes and the per-step launch sequence can be
-// captured once in a hipGraph.  A work item is the unit of the single-grid
-// row kernel (63 columns x a chunk of rows of one grid, one wavefront) and
-// runs exactly its code (row_item), with the grid's own dt, clock and
-// status, so a run's result is bit-identical to running it alone.
+// captured once in a hipGraph.  A 2D item is a tile of the single-grid tile
+// kernel (63 columns x R rows, corrections in place), a 1D item a tile of the
+// single-grid line kernel (46 cells, a whole step), with the grid's own dt,
+// clock and status, so a run's result is bit-identical to running it alone.
+// Bound: the FP64 issue and the chain of a tile, as there; a step is five
+// launches (fourteen with a list of flagged cells and a correction kernel per
+// stage: 320 us per step for 28 1D and 12 2D runs of 0.65 M cells).
 #pragma once
 #include "wl2_aux.hpp"
-#include "wl2_row.hpp"
-#include "wl2_row_launch.hpp"
+#include "wl2_line.hpp"
+#include "wl2_tile.hpp"
 
 namespace wl2 {
 
-// Device-resident descriptor of one admitted grid (one slot).
+// Device-resident descriptor of one admitted grid (one slot).  The arrays are
+// element offsets into the pool, which the kernels get as an argument (so
+// that they address it as global memory).
 struct BGrid {
   KGrid g;
   KPhys ph;
-  double* U;   // state U^n, updated in place by the third stage
-  double* U1;  // stage buffers
-  double* U2;
-  StepCtl* ctl;
+  long long U;   // state U^n, updated in place by the third stage
+  long long U1;  // stage buffers
+  long long U2;
   double cfl_dx;
   int dim, nv;
   int active;
@@ -27,12 +31,12 @@ struct BGrid {
 };
 
 constexpr int BATCH_MAX_SLOTS = 4096;
-constexpr int BATCH_CHUNK = 4096;  // cells per reduction chunk
+constexpr int BATCH_CHUNK = 1024;  // cells per reduction chunk
 
-// Work item of the batched row kernel: columns x0 .. x0+62 and rows y0 .. y1-1
-// of the grid in `slot`.
-struct RowItem {
-  int slot, x0, y0, y1;
+// Work item: 2D, columns x0 .. x0 + 62 and rows y0 .. of the grid in `slot`;
+// 1D, cells x0 .. x0 + 45.
+struct BatchItem {
+  int slot, x0, y0, pad;
 };
 
 // Reduction chunks: chunk c covers cells [first[c], first[c] + count[c]) of
@@ -45,84 +49,81 @@ struct BChunks {
   int* count;
 };
 
-// Stage `stage` of every item of one dimension (NV = 3: 1D runs, 4: 2D).
-// Stage pointers and RK coefficients of a run.
-struct StageRefs {
-  const double* Uk;
-  double* out;
-  double ra, rb;
-};
-
-__device__ __forceinline__ StageRefs stage_refs(const BGrid& G, int stage) {
-  StageRefs r;
-  r.Uk = stage == 0 ? G.U : (stage == 1 ? G.U1 : G.U2);
-  r.out = stage == 0 ? G.U1 : (stage == 1 ? G.U2 : G.U);
-  r.ra = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
-  r.rb = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
-  return r;
-}
-
-template <int NV>
-__global__ __launch_bounds__(RW, 2) void batch_row_kernel(const BGrid* __restrict__ grids,
-                                                         const RowItem* __restrict__ items,
-                                                         const int* n_items, int stage,
-                                                         unsigned long long* list,
-                                                         unsigned int* list_n) {
-  __shared__ double buf[NV + 3][RB];
-  __shared__ double ring[2][NV + 3][RW];
-  const int n = *n_items;
-  for (int k = blockIdx.x; k < n; k += gridDim.x) {
-    const RowItem it = items[k];
-    const BGrid& G = grids[it.slot];
-    const double dt = G.ctl->dt;
-    if (!(dt > 0.0)) continue;  // finished (or not started) run
-    const StageRefs sr = stage_refs(G, stage);
-    const RowArgs a{sr.Uk, sr.out, G.U, G.ctl, sr.ra, sr.rb, list, list_n,
-                    (unsigned long long)it.slot << 40, nullptr, nullptr};
-    // (a batch admits no grid with state sides: their checks compiled out)
-    if (G.ph.split == SPLIT_LLF && G.ph.hybrid == HYB_PER_FIELD)
-      row_item<NV, OUT_RK, 0, 0, false>(a, G.g, G.ph, buf, ring, it.x0, it.y0, it.y1, dt);
-    else
-      row_item<NV, OUT_RK, -1, -1, false>(a, G.g, G.ph, buf, ring, it.x0, it.y0, it.y1, dt);
-  }
-}
-
-// Nonlinear corrections of the cells listed in this stage by all runs
-// (entries slot << 40 | element offset << 8 | face mask): FIX_GRP lanes per
-// entry for a short list, a lane per entry for a long one (same bits).
-__global__ __launch_bounds__(128) void batch_fix_kernel(const BGrid* __restrict__ grids,
-                                                        const unsigned long long* __restrict__ list,
-                                                        const unsigned int* list_n, int stage) {
-  const unsigned int n = *list_n;
-  const unsigned int threads = gridDim.x * blockDim.x;
-  const unsigned int tid = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool grouped = (unsigned long long)n * FIX_GRP <= FIX_GROUPED_LANES && n <= threads / FIX_GRP;
-  const unsigned int step = grouped ? threads / FIX_GRP : threads;
-  for (unsigned int i = grouped ? tid / FIX_GRP : tid; i < n; i += step) {
-    const unsigned long long e = list[i];
-    const BGrid& G = grids[(int)(e >> 40)];
-    const double dt = G.ctl->dt;
-    if (!(dt > 0.0)) continue;
-    const StageRefs sr = stage_refs(G, stage);
-    const long long off = (long long)((e >> 8) & 0xffffffffull);
-    const unsigned cm = (unsigned)(e & 0xffu);
-    const bool fast = G.ph.split == SPLIT_LLF && G.ph.hybrid == HYB_PER_FIELD;
-    if (G.dim == 1) {
-      double un[3];
-      if (fast) row_fix_cell<3, 0, 0>(sr.Uk, sr.out, G.ctl, G.g, G.ph, off, cm, sr.rb * dt, grouped, un);
-      else row_fix_cell<3, -1, -1>(sr.Uk, sr.out, G.ctl, G.g, G.ph, off, cm, sr.rb * dt, grouped, un);
+// Stage STAGE of every 2D run; beside it, in stage 0 the whole step of every
+// 1D run (U to U1), in stage 1 its copy back (other items still read U before).
+// FAST: every admitted run has the default scheme (LLF splitting, per-field
+// switch, Eq.(28)), fixed at compile time; else the build that reads it at run
+// time serves them all (the same bits; both in one kernel spill: 52 us per
+// stage against 48).
+template <int R, int STAGE, bool FAST>
+__global__ __launch_bounds__((2 * R + 1) * 64, 4) void batch_stage_kernel(
+    const BGrid* __restrict__ grids, double* pool, StepCtl* ctls, const BatchItem* __restrict__ items1,
+    const BatchItem* __restrict__ items2, const int* __restrict__ n_items) {
+  constexpr int NW = 2 * R + 1;
+  constexpr size_t BYTES = sizeof(TileShared<R>) > NW * sizeof(LineShared) ? sizeof(TileShared<R>)
+                                                                           : NW * sizeof(LineShared);
+  __shared__ __attribute__((aligned(16))) char raw[BYTES];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int n1 = STAGE < 2 ? n_items[0] : 0, n1g = (n1 + NW - 1) / NW;  // a 1D item per wavefront
+  const int total = n1g + n_items[1];
+  for (int q = blockIdx.x; q < total; q += gridDim.x) {
+    if (q < n1g) {
+      const int i = q * NW + wave;
+      if (i < n1) {
+        const int slot = items1[i].slot, x0 = items1[i].x0;
+        const BGrid& G = grids[slot];
+        __builtin_assume(G.g.bc_lo[0] != BC_INFLOW);  // (not admitted)
+        const double dt = ctls[slot].dt;
+        if (dt > 0.0) {  // else a finished (or not started) run
+          const int n = G.g.n[0], k = x0 - LHALO + lane;
+          const bool own = lane >= LHALO && lane < LHALO + LT && k < n;
+          double* U = pool + G.U;
+          double* U1 = pool + G.U1;
+          double u[LNV];
+          if (STAGE == 0) {
+            int idx;
+            const bool cell = line_cell(G.g, k, idx);
+#pragma unroll
+            for (int v = 0; v < LNV; ++v) u[v] = U[(long long)v * n + idx];
+            LineShared& sh = reinterpret_cast<LineShared*>(raw)[wave];
+            line_tile<FAST ? SPLIT_LLF : -1, FAST ? HYB_PER_FIELD : -1, FAST ? W_L2IS : -1>(G.g, G.ph, x0, cell,
+                                                                                          dt, u, sh);
+            if (own) {
+#pragma unroll
+              for (int v = 0; v < LNV; ++v) U1[(long long)v * n + k] = u[v];
+            }
+          } else if (own) {
+#pragma unroll
+            for (int v = 0; v < LNV; ++v) U[(long long)v * n + k] = U1[(long long)v * n + k];
+          }
+        }
+      }
     } else {
-      double un[4];
-      if (fast) row_fix_cell<4, 0, 0>(sr.Uk, sr.out, G.ctl, G.g, G.ph, off, cm, sr.rb * dt, grouped, un);
-      else row_fix_cell<4, -1, -1>(sr.Uk, sr.out, G.ctl, G.g, G.ph, off, cm, sr.rb * dt, grouped, un);
+      const BatchItem it = items2[q - n1g];
+      const BGrid& G = grids[it.slot];
+      const KGrid g = G.g;
+      const KPhys ph = G.ph;
+      __builtin_assume(g.bc_lo[0] != BC_INFLOW);  // (not admitted)
+      TileArgs ta{};
+      ta.r.Uk = pool + (STAGE == 0 ? G.U : (STAGE == 1 ? G.U1 : G.U2));
+      ta.r.out = pool + (STAGE == 0 ? G.U1 : (STAGE == 1 ? G.U2 : G.U));
+      ta.r.Un = pool + G.U;
+      ta.r.ctl = ctls + it.slot;
+      ta.r.rk_a = STAGE == 0 ? 0.0 : (STAGE == 1 ? 0.75 : 1.0 / 3.0);
+      ta.r.rk_b = STAGE == 0 ? 1.0 : (STAGE == 1 ? 0.25 : 2.0 / 3.0);
+      TileShared<R>& sh = *reinterpret_cast<TileShared<R>*>(raw);
+      tile2d_item<R, OUT_RK, FAST ? SPLIT_LLF : -1, FAST ? HYB_PER_FIELD : -1, FAST ? W_L2IS : -1>(
+          ta, g, ph, it.x0, it.y0, false, sh);
     }
+    __syncthreads();  // the LDS is free for the next item
   }
 }
 
 // Per-grid CFL maximum over reduction chunks; one atomic per chunk.  The
 // per-cell arithmetic is the same as cfl_reduce_kernel (bit-identical dt).
-__global__ __launch_bounds__(RED_BLOCK) void batch_cfl_kernel(const BGrid* __restrict__ grids,
-                                                              BChunks ch, const int* nchunks) {
+static __global__ __launch_bounds__(RED_BLOCK) void batch_cfl_kernel(const BGrid* __restrict__ grids,
+                                                                     const double* pool, StepCtl* ctl,
+                                                                     BChunks ch, const int* nchunks) {
 #pragma clang fp contract(off)
   __shared__ double sh[RED_BLOCK / 64];
   const int n = *nchunks;
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(RED_BLOCK) void batch_cfl_kernel(const BGrid* __res
     const long long c0 = ch.first[c];
     const int cnt = ch.count[c];
     const long long nc = G.g.ncell;
-    const double* U = G.U;
+    const double* U = pool + G.U;
     const double gamma = G.ph.gamma;
     double smax = 0.0;
     bool bad = false;
@@ -146,20 +147,20 @@ __global__ __launch_bounds__(RED_BLOCK) void batch_cfl_kernel(const BGrid* __res
       }
     }
     const double bm = block_max(smax, sh);
-    if (threadIdx.x == 0 && (bm > 0.0 || bm != bm)) cfl_fold(G.ctl, bm);
-    if (bad) atomicOr(&G.ctl->status, 1u);
+    if (threadIdx.x == 0 && (bm > 0.0 || bm != bm)) cfl_fold(ctl + ch.cslot[c], bm);
+    if (bad) atomicOr(&ctl[ch.cslot[c]].status, 1u);
   }
 }
 
-// One thread per active slot: dt from its maximum, clipped to its own t_end
+// One wavefront per active slot: dt from its maximum, clipped to its own t_end
 // (dt = 0 once finished or after a non-physical state).
-[[maybe_unused]] static __global__ void batch_finalize_kernel(const BGrid* __restrict__ grids, const int* slots,
-                                      const int* nslots) {
+[[maybe_unused]] static __global__ __launch_bounds__(64) void batch_finalize_kernel(
+    const BGrid* __restrict__ grids, StepCtl* ctls, const int* slots, const int* nslots) {
   const int n = *nslots;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const BGrid& G = grids[slots[i]];
-    StepCtl* ctl = G.ctl;
-    double dt = G.cfl_dx / cfl_take(ctl);
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    StepCtl* ctl = ctls + slots[i];
+    double dt = grids[slots[i]].cfl_dx / cfl_take_wave(ctl);
+    if (threadIdx.x != 0) continue;
     const double t = ctl->t, te = ctl->t_end;
     if (!(t < te) || ctl->status != 0u || !(dt > 0.0)) {
       dt = 0.0;
@@ -179,11 +180,11 @@ struct SlotState {
   int slot;
 };
 
-[[maybe_unused]] static __global__ void batch_gather_kernel(const BGrid* __restrict__ grids, const int* slots,
+[[maybe_unused]] static __global__ void batch_gather_kernel(const StepCtl* ctls, const int* slots,
                                     const int* nslots, SlotState* out) {
   const int n = *nslots;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const StepCtl* ctl = grids[slots[i]].ctl;
+    const StepCtl* ctl = ctls + slots[i];
     out[i].t = ctl->t;
     out[i].t_end = ctl->t_end;
     out[i].status = ctl->status;

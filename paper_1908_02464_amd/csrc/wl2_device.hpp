@@ -142,19 +142,6 @@ __device__ __forceinline__ void cfl_clear(StepCtl* ctl) {
   for (int s = 0; s < CFL_SLOTS; ++s) ctl->smax[s].bits = 0ull;
 }
 
-// The running maximum over all slots, which are cleared for the next
-// reduction (one thread, after the folding launches have finished).
-__device__ __forceinline__ double cfl_take(StepCtl* ctl) {
-  unsigned long long m = 0ull;
-#pragma unroll
-  for (int s = 0; s < CFL_SLOTS; ++s) {
-    const unsigned long long b = ctl->smax[s].bits;
-    m = b > m ? b : m;
-  }
-  cfl_clear(ctl);
-  return __longlong_as_double((long long)m);
-}
-
 // The running maximum over all slots read by one whole wavefront (lane s
 // reads slot s; every lane gets the maximum), the slots left as they are.
 __device__ __forceinline__ double cfl_peek_wave(const StepCtl* ctl) {
@@ -164,22 +151,17 @@ __device__ __forceinline__ double cfl_peek_wave(const StepCtl* ctl) {
   return wave_max(lane < CFL_SLOTS ? __longlong_as_double((long long)ctl->smax[lane].bits) : 0.0);
 }
 
-// cfl_take by one whole wavefront (lane s reads and clears slot s): one
-// round trip to memory instead of CFL_SLOTS.  Every lane gets the maximum.
+// The same, the slots cleared for the next reduction (lane s reads and clears
+// slot s).
 __device__ __forceinline__ double cfl_take_wave(StepCtl* ctl) {
   static_assert(CFL_SLOTS <= 64, "one slot per lane");
   const int lane = threadIdx.x & 63;
-  unsigned long long m = 0ull;
+  double m = 0.0;
   if (lane < CFL_SLOTS) {
-    m = ctl->smax[lane].bits;
+    m = __longlong_as_double((long long)ctl->smax[lane].bits);
     ctl->smax[lane].bits = 0ull;
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long q = __shfl_xor(m, o, 64);
-    m = q > m ? q : m;
-  }
-  return __longlong_as_double((long long)m);
+  return wave_max(m);
 }
 
 // The device-clock dt of a step from the CFL maximum folded by the step

@@ -223,25 +223,92 @@ __device__ __forceinline__ void line_fold(LineCtl::Slot* set, double smax, bool 
   }
 }
 
+// LDS of a wavefront's tile.
+struct LineShared {
+  double rec[(LNV + 3) * LP];
+  FaceScratch<LNV> scr;
+  double roe[LNV][64];
+};
+
+// Index of the cell at line position k of the lane (periodic images wrap,
+// positions past the other sides are clamped), and whether it evolves: an
+// in-grid cell or a periodic image of one.
+__device__ __forceinline__ bool line_cell(const KGrid& g, int k, int& idx) {
+  const int n = g.n[0];
+  if (g.bc_lo[0] == BC_PERIODIC) {
+    idx = k % n;
+    if (idx < 0) idx += n;
+    return true;
+  }
+  idx = k < 0 ? 0 : (k >= n ? n - 1 : k);
+  return k >= 0 && k < n;
+}
+
+// The three stages of one step on the tile of cells x0 .. x0 + LT - 1 (lane l
+// holds cell x0 - LHALO + l in u, replaced by its new state).
+template <int SPLIT, int HYB, int W>
+__device__ __forceinline__ void line_tile(const KGrid& g, const KPhys& ph, int x0, bool cell, double dt,
+                                          double (&u)[LNV], LineShared& sh) {
+  const int lane = threadIdx.x & 63, n = g.n[0], k = x0 - LHALO + lane;
+  const bool per = g.bc_lo[0] == BC_PERIODIC;
+  double* rec = sh.rec;
+  double un[LNV];
+  // ghosts: the lane of the cell they mirror (in the tile wherever the ghost
+  // is needed), or the inflow state
+  bool flip = false;
+  const bool ghost = !cell && k >= -3 && k < n + 3;
+  const bool inflow = ghost && k < 0 && g.bc_lo[0] == BC_INFLOW;
+  int src = ghost ? ghost_index(k, n, g.bc_lo[0], g.bc_hi[0], flip) - (x0 - LHALO) : 0;
+  src = src < 0 ? 0 : (src > 63 ? 63 : src);
+  if (inflow) {
+    load_inflow<LNV>(g, 0, u);
+    flip = false;
+  }
+#pragma unroll
+  for (int v = 0; v < LNV; ++v) un[v] = u[v];
+#pragma unroll 1
+  for (int st = 0; st < 3; ++st) {
+    double ra, rb;
+    line_rk(st, ra, rb);
+    LRec<LNV> r;
+    make_lrec<LNV>(u, ph, r);
+    lane_put<LNV, LP>(rec + lane + 3, r);
+    wave_lds_fence();
+    if (ghost && !inflow) {
+      LaneSrc<LNV, LP>{rec + src + 3, 1}.get(0, r);
+      if (flip) r.U[1] = -r.U[1];
+      lane_put<LNV, LP>(rec + lane + 3, r);
+    }
+    wave_lds_fence();
+    const int lo = 3 * (st + 1), hi = 64 - lo;  // cells updated by this stage
+    double F60[LNV], dF[LNV], Fr[LNV], dr[LNV];
+    const bool face = lane >= lo && lane <= hi && (per || (k >= 0 && k <= n));
+    const bool m = wave_face<LNV, 0, LP, SPLIT, HYB, W>(rec, 1, face, ph, nullptr, sh.scr, sh.roe, F60, dF);
+    const unsigned long long mw = __ballot(m);
+    const bool mr = ((mw >> lane) & 2ull) != 0ull;
+#pragma unroll
+    for (int v = 0; v < LNV; ++v) {
+      Fr[v] = next_lane(F60[v]);
+      dr[v] = 0.0;
+    }
+    if (mw != 0ull) {
+#pragma unroll
+      for (int v = 0; v < LNV; ++v) dr[v] = next_lane(dF[v]);
+    }
+    if (cell && lane >= lo && lane < hi) line_update(u, un, F60, Fr, m, mr, dF, dr, ra, rb, dt, ph);
+  }
+}
+
 // One step.  Bound: a chain of three stages of ~250 dependent FP64 operations
 // each (~750 with WENO faces) on one wavefront per SIMD, plus the launch.
 template <int SPLIT, int HYB, int W>
 __global__ __launch_bounds__(64) void line_step_kernel(LineStepArgs a, KGrid g, KPhys ph) {
-  __shared__ double rec[(LNV + 3) * LP];
-  __shared__ FaceScratch<LNV> scr;
-  __shared__ double roe[LNV][64];
+  __shared__ LineShared sh;
   const int lane = threadIdx.x, n = g.n[0];
   const int x0 = blockIdx.x * LT, k = x0 - LHALO + lane;
-  const bool per = g.bc_lo[0] == BC_PERIODIC;
-  const bool cell = per || (k >= 0 && k < n);  // an evolved cell, or a periodic image of one
-  int idx = k;
-  if (per) {
-    idx = k % n;
-    if (idx < 0) idx += n;
-  } else {
-    idx = idx < 0 ? 0 : (idx >= n ? n - 1 : idx);
-  }
-  double u[LNV], un[LNV];
+  int idx;
+  const bool cell = line_cell(g, k, idx);
+  double u[LNV];
 #pragma unroll
   for (int v = 0; v < LNV; ++v) u[v] = a.U[(long long)v * n + idx];
   const bool own = lane >= LHALO && lane < LHALO + LT && k < n;  // cells stored here
@@ -283,50 +350,7 @@ __global__ __launch_bounds__(64) void line_step_kernel(LineStepArgs a, KGrid g, 
     return;
   }
 
-  // ghosts: the lane of the cell they mirror (in the tile wherever the ghost
-  // is needed), or the inflow state
-  bool flip = false;
-  const bool ghost = !cell && k >= -3 && k < n + 3;
-  const bool inflow = ghost && k < 0 && g.bc_lo[0] == BC_INFLOW;
-  int src = ghost ? ghost_index(k, n, g.bc_lo[0], g.bc_hi[0], flip) - (x0 - LHALO) : 0;
-  src = src < 0 ? 0 : (src > 63 ? 63 : src);
-  if (inflow) {
-    load_inflow<LNV>(g, 0, u);
-    flip = false;
-  }
-#pragma unroll
-  for (int v = 0; v < LNV; ++v) un[v] = u[v];
-#pragma unroll 1
-  for (int st = 0; st < 3; ++st) {
-    double ra, rb;
-    line_rk(st, ra, rb);
-    LRec<LNV> r;
-    make_lrec<LNV>(u, ph, r);
-    lane_put<LNV, LP>(rec + lane + 3, r);
-    wave_lds_fence();
-    if (ghost && !inflow) {
-      LaneSrc<LNV, LP>{rec + src + 3, 1}.get(0, r);
-      if (flip) r.U[1] = -r.U[1];
-      lane_put<LNV, LP>(rec + lane + 3, r);
-    }
-    wave_lds_fence();
-    const int lo = 3 * (st + 1), hi = 64 - lo;  // cells updated by this stage
-    double F60[LNV], dF[LNV], Fr[LNV], dr[LNV];
-    const bool face = lane >= lo && lane <= hi && (per || (k >= 0 && k <= n));
-    const bool m = wave_face<LNV, 0, LP, SPLIT, HYB, W>(rec, 1, face, ph, nullptr, scr, roe, F60, dF);
-    const unsigned long long mw = __ballot(m);
-    const bool mr = ((mw >> lane) & 2ull) != 0ull;
-#pragma unroll
-    for (int v = 0; v < LNV; ++v) {
-      Fr[v] = next_lane(F60[v]);
-      dr[v] = 0.0;
-    }
-    if (mw != 0ull) {
-#pragma unroll
-      for (int v = 0; v < LNV; ++v) dr[v] = next_lane(dF[v]);
-    }
-    if (cell && lane >= lo && lane < hi) line_update(u, un, F60, Fr, m, mr, dF, dr, ra, rb, dt, ph);
-  }
+  line_tile<SPLIT, HYB, W>(g, ph, x0, cell, dt, u, sh);
   double smx = 0.0;
   bool bad = false;
   if (own) {

@@ -35,7 +35,7 @@ hipError_t row_reset(const RowLaunch& L) {
 
 hipError_t row_fix(const RowLaunch& L) {
   const RowArgs a{L.Uk,   L.out,    L.Un, L.ctl,        L.rk_a,
-                  L.rk_b, L.list,   L.list_n, 0ull, L.list_clear,
+                  L.rk_b, L.list,   L.list_n, L.list_clear,
                   L.out_kind == OUT_RK ? L.cfl : nullptr, L.out_kind == OUT_RK ? L.clock : nullptr,
                   L.cfl_dx, L.s_floor};
   const dim3 fg(1024), fb(128);
@@ -86,7 +86,7 @@ hipError_t row_fix(const RowLaunch& L) {
 
 hipError_t row_launch(const RowLaunch& L) {
   const RowArgs a{L.Uk,   L.out,  L.Un,     L.ctl, L.rk_a,
-                  L.rk_b, L.list, L.list_n, 0ull,  nullptr,
+                  L.rk_b, L.list, L.list_n, nullptr,
                   L.out_kind == OUT_RK ? L.cfl : nullptr, L.out_kind == OUT_RK ? L.clock : nullptr,
                   L.cfl_dx, L.s_floor};
   const int tiles_x = (L.g.n[0] + RT - 1) / RT;

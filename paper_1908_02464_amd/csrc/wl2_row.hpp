@@ -1,6 +1,6 @@
 // Fused 1D/2D stage kernel (gfx950, FP64): both sweep directions, the flux
 // difference of Eq.(19) and the SSP-RK3 stage combination in one pass over
-// HBM, for one grid (row_kernel) or for many grids (the batched form).
+// HBM.
 //
 // Work item: one wavefront owns RT = 63 consecutive columns of one grid and
 // marches along y through a chunk of rows (1D: the single row).  Each lane
@@ -34,7 +34,6 @@ struct RowArgs {
   double rk_a, rk_b;   // RK: out = rk_a U^n + rk_b (Uk + dt dU)
   unsigned long long* list;  // cells next to a face that needs the WENO flux
   unsigned int* list_n;      // entries in list
-  unsigned long long tag;    // or-ed into every entry (the batch slot << 40)
   unsigned int* list_clear;  // if set: the next stage's counter, zeroed by the
                              // correction kernel
   StepCtl* cfl;              // RK: if set, fold the CFL speed of the new state
@@ -47,7 +46,7 @@ struct RowArgs {
   double cfl_dx, s_floor;
 };
 
-// Entry of the correction list: tag | element offset << 8 | face mask (bit 0
+// Entry of the correction list: element offset << 8 | face mask (bit 0
 // x-, 1 x+, 2 y-, 3 y+).  Appended with one atomic per wavefront.
 __device__ __forceinline__ void list_append(const RowArgs& a, long long off, unsigned cm) {
   const unsigned long long ball = __ballot(cm != 0u);
@@ -59,7 +58,7 @@ __device__ __forceinline__ void list_append(const RowArgs& a, long long off, uns
   base = __shfl(base, leader, RW);
   if (cm) {
     const unsigned int rank = __popcll(ball & ((1ull << lane) - 1ull));
-    a.list[base + rank] = a.tag | ((unsigned long long)off << 8) | cm;
+    a.list[base + rank] = ((unsigned long long)off << 8) | cm;
   }
 }
 
@@ -124,7 +123,7 @@ struct Win6Src {  // six records in registers
 
 // Raw cell (column element offset xy, row y) of a 2D grid, ghost-mapped in
 // y; the mirror flip of the y momentum is reported, not applied.
-template <int NV, bool YS = true>
+template <int NV>
 __device__ __forceinline__ void row_load_raw(const double* __restrict__ U, const KGrid& g,
                                              long long xy, int y, double (&u)[NV]) {
   bool fy = false;
@@ -132,9 +131,8 @@ __device__ __forceinline__ void row_load_raw(const double* __restrict__ U, const
   const long long off = xy + (long long)iy * g.stride[1];
 #pragma unroll
   for (int v = 0; v < NV; ++v) u[v] = U[v * g.ncell + off];
-  // state ghosts of a y side (2D grids: xy is the column's x; YS false: the
-  // caller's grids have none, and the check is compiled out)
-  if (YS && NV == 4 && (y < 0 || y >= g.n[1]) && is_yghost(g, y)) load_yghost<NV>(g, xy, y, u);
+  // state ghosts of a y side (2D grids: xy is the column's x)
+  if (NV == 4 && (y < 0 || y >= g.n[1]) && is_yghost(g, y)) load_yghost<NV>(g, xy, y, u);
 }
 
 template <int NV>
@@ -150,7 +148,7 @@ __device__ __forceinline__ void row_flip(const KGrid& g, bool fx, int y, double 
 // and the stage combination; cells next to a flagged face are listed.
 // Called by whole wavefronts; `buf` is the item's LDS row buffer [NV+3][RB],
 // `ring` its window ring [2][NV+3][RW] (2D).
-template <int NV, int OUT, int SPLIT, int HYB, bool YS = true>
+template <int NV, int OUT, int SPLIT, int HYB>
 __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const KPhys& ph,
                                          double (*buf)[RB], double (*ring)[NV + 3][RW], int x0,
                                          int y0, int y1, double dt) {
@@ -178,14 +176,14 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
   if constexpr (NV == 3) {
     // 1D: one row
     double u[NV];
-    row_load_raw<NV, YS>(a.Uk, g, oxy, 0, u);
+    row_load_raw<NV>(a.Uk, g, oxy, 0, u);
     row_flip<NV>(g, fx, 0, u);
     LRec<NV> own_rec;
     make_lrec<NV>(u, ph, own_rec);
     row_put<NV>(buf, lane + 3, own_rec);
     if (halo) {
       double hu[NV];
-      row_load_raw<NV, YS>(a.Uk, g, hxy, 0, hu);
+      row_load_raw<NV>(a.Uk, g, hxy, 0, hu);
       row_flip<NV>(g, fxh, 0, hu);
       if (hin) load_inflow<NV>(g, 0, hu);
       LRec<NV> hr;
@@ -237,25 +235,25 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
     {
       LRec<NV> cm3, cm2, cm1;
       double u[NV];
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 - 3, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 - 3, u);
       row_flip<NV>(g, fx, y0 - 3, u);
       make_lrec<NV>(u, ph, cm3);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 - 2, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 - 2, u);
       row_flip<NV>(g, fx, y0 - 2, u);
       make_lrec<NV>(u, ph, cm2);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 - 1, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 - 1, u);
       row_flip<NV>(g, fx, y0 - 1, u);
       make_lrec<NV>(u, ph, cm1);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0, u);
       row_flip<NV>(g, fx, y0, u);
       make_lrec<NV>(u, ph, r0);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 + 1, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 + 1, u);
       row_flip<NV>(g, fx, y0 + 1, u);
       make_lrec<NV>(u, ph, r1);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 + 2, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 + 2, u);
       row_flip<NV>(g, fx, y0 + 2, u);
       make_lrec<NV>(u, ph, r2);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 + 3, u);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 + 3, u);
       row_flip<NV>(g, fx, y0 + 3, u);
       make_lrec<NV>(u, ph, r3);
       ring_put<NV>(ring, (y0 - 2) & 1, lane, cm2);
@@ -263,8 +261,8 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       // face y0 - 1/2: cells y0-3 .. y0+2
       const LRec<NV> wp[6] = {cm3, cm2, cm1, r0, r1, r2};
       yprev = face_linear_l<NV, 1, SPLIT, HYB>(Win6Src<NV>{wp}, ph, ph.eps_thr[1], lfy, Fyp);
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y0 + 4, upre);
-      if (halo) row_load_raw<NV, YS>(a.Uk, g, hxy, y0, hpre);
+      row_load_raw<NV>(a.Uk, g, oxy, y0 + 4, upre);
+      if (halo) row_load_raw<NV>(a.Uk, g, hxy, y0, hpre);
     }
     for (int y = y0; y < y1; ++y) {
       row_put<NV>(buf, lane + 3, r0);  // cell (x, y)
@@ -275,7 +273,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
         make_lrec<NV>(hpre, ph, hr);
         row_put<NV>(buf, hslot, hr);
         asm volatile("" ::: "memory");  // the prefetch below stays after this use
-        row_load_raw<NV, YS>(a.Uk, g, hxy, y + 1, hpre);
+        row_load_raw<NV>(a.Uk, g, hxy, y + 1, hpre);
       }
       __syncthreads();
       __builtin_amdgcn_s_setprio(0);
@@ -335,42 +333,32 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       make_lrec<NV>(upre, ph, r3);
       asm volatile("" ::"v"(r3.U[0]), "v"(r3.U[NV - 1]), "v"(r3.p), "v"(r3.c), "v"(r3.iw)
                    : "memory");
-      row_load_raw<NV, YS>(a.Uk, g, oxy, y + 5, upre);
+      row_load_raw<NV>(a.Uk, g, oxy, y + 5, upre);
       __syncthreads();  // row buffer free for the next row
     }
   }
   if (OUT == OUT_RK && a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
 }
 
-// Lanes per listed cell in the correction kernels for short lists (one per
-// face).
-constexpr int FIX_GRP = 4;
-
 // Nonlinear part of the flux of the flagged faces of one listed cell at
 // element offset `off` (face order x-, x+, y-, y+, as in the 3D correction
-// kernel), added to the output; `scale` = rk_b dt for a stage, 1 for dU/dt.
-// grouped: FIX_GRP lanes share the cell (one face each) and the group's first
-// lane writes; else one lane does all.  Each face is recomputed from the
-// stage input by both of its cells with the same operations, so both get
-// the same bits.  Returns true on the lane that wrote, with the new state in
-// un.
+// kernel), added to the output by one lane; `scale` = rk_b dt for a stage, 1
+// for dU/dt; the new state in un.  Each face is recomputed from the stage
+// input by both of its cells with the same operations, so both get the same
+// bits.
 template <int NV, int SPLIT, int HYB>
-__device__ __forceinline__ bool row_fix_cell(const double* Uk, double* out, const StepCtl* ctl,
+__device__ __forceinline__ void row_fix_cell(const double* Uk, double* out, const StepCtl* ctl,
                                              const KGrid& g, const KPhys& ph, long long off,
-                                             unsigned cm, double scale, bool grouped,
-                                             double (&un)[NV]) {
+                                             unsigned cm, double scale, double (&un)[NV]) {
   const int x = (int)(off % g.n[0]);
   const int y = (int)(off / g.n[0]);
   double acc[NV];
-  if (grouped) grouped_correction<NV, FIX_GRP, SPLIT, HYB>(Uk, g, ph, ctl, x, y, 0, cm, acc);
-  else serial_correction<NV, SPLIT, HYB>(Uk, g, ph, ctl, x, y, 0, cm, acc);
-  if (grouped && (threadIdx.x % FIX_GRP) != 0) return false;
+  serial_correction<NV, SPLIT, HYB>(Uk, g, ph, ctl, x, y, 0, cm, acc);
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     un[v] = out[v * g.ncell + off] + scale * (acc[v] * ph.inv_dx);
     out[v * g.ncell + off] = un[v];
   }
-  return true;
 }
 
 // Listed cells per workgroup round of the field-parallel mode: the two
@@ -479,10 +467,9 @@ __global__ __launch_bounds__(128) void row_fix_kernel(RowArgs a, KGrid g, KPhys 
     for (unsigned int i = tid; i < n; i += threads) {
       const unsigned long long e = a.list[i];
       double un[NV];
-      const bool wrote = row_fix_cell<NV, SPLIT, HYB>(a.Uk, a.out, a.ctl, g, ph,
-                                                      (long long)((e >> 8) & 0xffffffffull),
-                                                      (unsigned)(e & 0xffu), scale, false, un);
-      if (OUT == OUT_RK && a.cfl != nullptr && wrote)
+      row_fix_cell<NV, SPLIT, HYB>(a.Uk, a.out, a.ctl, g, ph, (long long)((e >> 8) & 0xffffffffull),
+                                   (unsigned)(e & 0xffu), scale, un);
+      if (OUT == OUT_RK && a.cfl != nullptr)
         cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
     }
   }

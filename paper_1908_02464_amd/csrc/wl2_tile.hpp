@@ -34,19 +34,29 @@ struct TileArgs {
   LfSlot* lf_clear;    // set that the stage before read, cleared for the next one
 };
 
-// Record row k (0 .. R + 5) holds grid row y0 - 3 + k; position c column x0 - 3 + c.
+template <int R>
+struct TileShared {
+  static constexpr int NW = 2 * R + 1;
+  double rec[(R + 6) * TROW];
+  double sF[NW][TV][64];         // first a wavefront's scratch, then its fluxes
+  FaceScratch<TV> scr[NW];       // dv of a wavefront: later its dF
+  unsigned long long smask[NW];  // flagged faces of a wavefront
+};
+
+// The tile of columns x0 .. and rows y0 ..; record row k (0 .. R + 5) holds
+// grid row y0 - 3 + k; position c column x0 - 3 + c.  lead: this workgroup
+// writes what one of the grid writes (clock, cleared slots).
 template <int R, int OUT, int SPLIT, int HYB, int W>
-__global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta, KGrid g, KPhys ph,
-                                                                    int tiles_x) {
+__device__ __forceinline__ void tile2d_item(const TileArgs& ta, const KGrid& g, const KPhys& ph, int x0,
+                                            int y0, bool lead, TileShared<R>& sh) {
   constexpr int NV = TV, NW = 2 * R + 1, ROWS = R + 6;
   const RowArgs& a = ta.r;
-  __shared__ double rec[ROWS * TROW];
-  __shared__ double sF[NW][NV][64];  // first a wavefront's scratch, then its fluxes
-  __shared__ FaceScratch<NV> scr[NW];      // dv of a wavefront: later its dF
-  __shared__ unsigned long long smask[NW];  // flagged faces of a wavefront
+  double* rec = sh.rec;
+  double (*sF)[NV][64] = sh.sF;
+  FaceScratch<NV>* scr = sh.scr;
+  unsigned long long* smask = sh.smask;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // scalar: so are its rows
-  const int x0 = (blockIdx.x % tiles_x) * RT, y0 = (blockIdx.x / tiles_x) * R;
   const int rows = min(R, g.n[1] - y0);
 
   // loads: record rows (64 columns x0 .. x0 + 63 each) and, last, the five
@@ -106,7 +116,7 @@ __global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta
 #pragma unroll
       for (int k = 0; k < NV; ++k) lf[k] = a.ctl->lf_bits[d][k];
     }
-    if (ta.lf_clear != nullptr && blockIdx.x == 0 && threadIdx.x < LF_SLOTS) ta.lf_clear[threadIdx.x] = LfSlot{};
+    if (ta.lf_clear != nullptr && lead && threadIdx.x < LF_SLOTS) ta.lf_clear[threadIdx.x] = LfSlot{};
   }
   // U^n of the cell this lane updates
   const int uy = y0 + wave;
@@ -120,10 +130,10 @@ __global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta
   double dt = 0.0;
   if (OUT == OUT_RK) {
     dt = a.clock != nullptr
-             ? clock_dt_wave(a.clock, a.cfl_dx, a.s_floor, blockIdx.x == 0 && threadIdx.x == 0)
+             ? clock_dt_wave(a.clock, a.cfl_dx, a.s_floor, lead && threadIdx.x == 0)
              : a.ctl->dt;
     if (!(dt > 0.0)) return;  // finished run: leave the state untouched (uniform)
-    if (ta.commit != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clock_commit(ta.commit);
+    if (ta.commit != nullptr && lead && threadIdx.x == 0) clock_commit(ta.commit);
   }
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -204,6 +214,14 @@ __global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta
     if (ta.lf_out != nullptr) lf_commit_wave<NV - 2>(ta.lf_out, mx);
     if (a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
   }
+}
+
+template <int R, int OUT, int SPLIT, int HYB, int W>
+__global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta, KGrid g, KPhys ph,
+                                                                    int tiles_x) {
+  __shared__ TileShared<R> sh;
+  tile2d_item<R, OUT, SPLIT, HYB, W>(ta, g, ph, (blockIdx.x % tiles_x) * RT, (blockIdx.x / tiles_x) * R,
+                                     blockIdx.x == 0, sh);
 }
 
 }  // namespace wl2
