@@ -294,25 +294,35 @@ bool use_line_steps(const weno_l2is_ctx* c) {
 // extra launch.
 constexpr long long FACE_ONCE_MIN_CELLS = 1ll << 17;
 
-// Rows per work item of the 1D/2D kernel: the tuned value, else the largest
-// of 6 .. 2 that still gives >= 1536 items, three quarters of the 2048
-// wavefronts the chip holds at once (measured: 6 rows at 1024^2 and 2048^2,
-// 3 at 512^2, 2 at 256^2; longer marches amortise the six-cell start of a
-// column, more items fill the chip).
+// Rows per work item of the 2D row kernel: the tuned value, else the y of 4
+// .. 20 with the least estimated time.  One wavefront per item and two per
+// SIMD: 2048 items run at once, in rounds of about y + 1.5 rows' time (the
+// 1.5: an item's first window and its first y face); a last round of at most
+// one wavefront per SIMD takes about 0.8 of a full one, one of more a full
+// one.  Measured against a sweep of y (us per step, chosen / 11 rows / best):
+// 1024^2 9 rows 166/174/166, 1200x800 8 rows 158/170/158, 1531x1013 13 rows
+// 206/251/206, 2048^2 17 rows 423/425/423, 3000x1700 20 rows 495/521/495,
+// 4096x1000 17 rows 424/424/424.  Beyond 20 rows an item's tail leaves more
+// of the chip idle than its window costs.
 int row_ych(const weno_l2is_ctx* c) {
   if (c->dim == 1) return 1;
   const int cap = ROW_MAX_YCH < c->n[1] ? ROW_MAX_YCH : c->n[1];
   if (c->zchunk > 0) return c->zchunk < cap ? c->zchunk : cap;
-  // One wavefront per item and two per SIMD: 2048 items run at once.  If
-  // the grid fits one such round with at most 12 rows per item, the fewest
-  // rows that do (the most parallel single round); otherwise 11 rows (fewer
-  // warm-up rows per row computed; items then run in several rounds).
   constexpr long long ROUND = 2048;
   const long long tiles = (c->n[0] + ROW_TILE - 1) / ROW_TILE;
-  const int ymax = 12 < cap ? 12 : cap;
-  for (int y = 2; y <= ymax; ++y)
-    if (tiles * ((c->n[1] + y - 1) / y) <= ROUND) return y;
-  return 11 < cap ? 11 : cap;
+  int best = cap < 4 ? cap : 4;
+  long long least = 0;
+  for (int y = best; y <= 20 && y <= cap; ++y) {
+    const long long items = tiles * ((c->n[1] + y - 1) / y);
+    const long long rest = items % ROUND;
+    const long long tenths = items / ROUND * 10 + (rest == 0 ? 0 : rest <= ROUND / 2 ? 8 : 10);
+    const long long cost = tenths * (2 * y + 3);
+    if (least == 0 || cost < least) {
+      least = cost;
+      best = y;
+    }
+  }
+  return best;
 }
 
 // The counters of the next stage launch, clearing both if needed.

@@ -114,6 +114,9 @@ __device__ __forceinline__ double dpp_move(double v) {
 
 // The value of the next lane (lane 63 keeps its own).
 __device__ __forceinline__ double next_lane(double v) { return dpp_move<0x130>(v); }  // wave_shl:1
+__device__ __forceinline__ int next_lane_int(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x130, 0xf, 0xf, false);
+}
 
 // Maximum over the 64 lanes, in every lane (all lanes active): row shifts by
 // 1, 2, 4, 8, then the last lane of each row of 16 to the rows above it.

@@ -19,6 +19,7 @@
 // applied at use.
 #pragma once
 #include "wl2_lface.hpp"
+#include "wl2_wface.hpp"
 
 namespace wl2 {
 
@@ -46,20 +47,35 @@ struct RowArgs {
   double cfl_dx, s_floor;
 };
 
-// Entry of the correction list: element offset << 8 | face mask (bit 0
-// x-, 1 x+, 2 y-, 3 y+).  Appended with one atomic per wavefront.
-__device__ __forceinline__ void list_append(const RowArgs& a, long long off, unsigned cm) {
+// Entry of the correction list: element offset << 8 | face mask (bit 0 x-, 1
+// x+, 2 y-, 3 y+).  A wavefront collects its entries in LDS (buf, n of them)
+// and moves them to the list with one atomic when LIST_BUF fills up and at
+// the end of its item: an atomic per row, all on one counter, had each
+// wavefront on a shock wait for one round trip per row (33 -> 42 us per stage
+// at 1024^2).
+constexpr int LIST_BUF = 256;
+
+__device__ __forceinline__ void list_flush(const RowArgs& a, unsigned long long* buf, int& n) {
+  if (n == 0) return;
+  const int lane = threadIdx.x & (RW - 1);
+  unsigned int base = 0;
+  if (lane == 0) base = atomicAdd(a.list_n, (unsigned int)n);
+  base = (unsigned int)__builtin_amdgcn_readfirstlane((int)base);
+  wave_lds_fence();
+  for (int i = lane; i < n; i += RW) a.list[base + i] = buf[i];
+  wave_lds_fence();
+  n = 0;
+}
+
+__device__ __forceinline__ void list_append(const RowArgs& a, unsigned long long* buf, int& n, long long off,
+                                            unsigned cm) {
   const unsigned long long ball = __ballot(cm != 0u);
   if (!ball) return;
   const int lane = threadIdx.x & (RW - 1);
-  const int leader = __ffsll((long long)ball) - 1;
-  unsigned int base = 0;
-  if (lane == leader) base = atomicAdd(a.list_n, (unsigned int)__popcll(ball));
-  base = __shfl(base, leader, RW);
-  if (cm) {
-    const unsigned int rank = __popcll(ball & ((1ull << lane) - 1ull));
-    a.list[base + rank] = ((unsigned long long)off << 8) | cm;
-  }
+  const int rank = __popcll(ball & ((1ull << lane) - 1ull));
+  if (cm) buf[n + rank] = ((unsigned long long)off << 8) | cm;
+  n += __popcll(ball);
+  if (n > LIST_BUF - RW) list_flush(a, buf, n);
 }
 
 template <int NV>
@@ -121,6 +137,17 @@ struct Win6Src {  // six records in registers
   __device__ __forceinline__ void get(int m, LRec<NV>& r) const { r = w[m]; }
 };
 
+// Row iy (in the grid) of the column at x: the row's address is uniform in the
+// wavefront and the column a 32-bit byte offset (nx <= 2^29: a larger grid's
+// arrays do not fit the device).
+template <int NV>
+__device__ __forceinline__ void row_load_in(const double* __restrict__ U, const KGrid& g, unsigned x8, int iy,
+                                            double (&u)[NV]) {
+  const char* p = (const char*)(U + (long long)iy * g.stride[1]);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) u[v] = *(const double*)(p + v * g.ncell * 8 + x8);
+}
+
 // Raw cell (column element offset xy, row y) of a 2D grid, ghost-mapped in
 // y; the mirror flip of the y momentum is reported, not applied.
 template <int NV>
@@ -147,11 +174,12 @@ __device__ __forceinline__ void row_flip(const KGrid& g, bool fx, int y, double 
 // (1D: y0 = 0, y1 = 1): the linear-branch fluxes of all its faces, Eq.(19)
 // and the stage combination; cells next to a flagged face are listed.
 // Called by whole wavefronts; `buf` is the item's LDS row buffer [NV+3][RB],
-// `ring` its window ring [2][NV+3][RW] (2D).
+// `ring` its window ring [2][NV+3][RW] (2D), `lbuf` its list entries.
 template <int NV, int OUT, int SPLIT, int HYB>
 __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const KPhys& ph,
-                                         double (*buf)[RB], double (*ring)[NV + 3][RW], int x0,
-                                         int y0, int y1, double dt) {
+                                         double (*buf)[RB], double (*ring)[NV + 3][RW],
+                                         unsigned long long* lbuf, int x0, int y0, int y1, double dt) {
+  int ln = 0;  // entries in lbuf
   const int lane = threadIdx.x & (RW - 1);
   const unsigned long long* lfx = a.ctl->lf_bits[0];
   const unsigned long long* lfy = a.ctl->lf_bits[1];
@@ -170,6 +198,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
   const bool hin = halo && x0 - 3 + hslot < 0 && g.bc_lo[0] == BC_INFLOW;
   const long long oxy = cx;  // row 0 element offset of the column (x stride 1)
   const long long hxy = hx;
+  const unsigned cx8 = (unsigned)cx * 8u, hx8 = (unsigned)hx * 8u;
   double cfl_max = 0.0;  // CFL speed of the cells written here (a.cfl set)
   bool cfl_bad = false;
 
@@ -201,10 +230,10 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
         face_linear_l<NV, 0, SPLIT, HYB>(RowSrc<NV>{buf, lane}, ph, ph.eps_thr[0], lfx, Fx);
     double Fr[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Fr[v] = __shfl_down(Fx[v], 1, RW);
-    const int mxr = __shfl_down((int)mx, 1, RW);
+    for (int v = 0; v < NV; ++v) Fr[v] = next_lane(Fx[v]);
+    const int mxr = next_lane_int((int)mx);
     const unsigned cm = own ? ((mx ? 1u : 0u) | (mxr ? 2u : 0u)) : 0u;
-    list_append(a, oxy, cm);
+    list_append(a, lbuf, ln, oxy, cm);
     if (own) {
       double un[NV];
 #pragma unroll
@@ -261,19 +290,30 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       // face y0 - 1/2: cells y0-3 .. y0+2
       const LRec<NV> wp[6] = {cm3, cm2, cm1, r0, r1, r2};
       yprev = face_linear_l<NV, 1, SPLIT, HYB>(Win6Src<NV>{wp}, ph, ph.eps_thr[1], lfy, Fyp);
-      row_load_raw<NV>(a.Uk, g, oxy, y0 + 4, upre);
-      if (halo) row_load_raw<NV>(a.Uk, g, hxy, y0, hpre);
+      if (halo) row_load_in<NV>(a.Uk, g, hx8, y0, hpre);
     }
+    bool fyn = false;  // the prefetched cell is a mirror ghost
+    auto prefetch = [&](int y) {
+      fyn = false;
+      if (y < g.n[1]) {
+        row_load_in<NV>(a.Uk, g, cx8, y, upre);
+      } else {  // past the grid (uniform)
+        const int iy = ghost_clamped(y, g.n[1], g.bc_lo[1], g.bc_hi[1], fyn);
+        row_load_in<NV>(a.Uk, g, cx8, iy, upre);
+        if (NV == 4 && is_yghost(g, y)) load_yghost<NV>(g, oxy, y, upre);
+      }
+    };
+    prefetch(y0 + 4);
     for (int y = y0; y < y1; ++y) {
       row_put<NV>(buf, lane + 3, r0);  // cell (x, y)
       if (halo) {
-        row_flip<NV>(g, fxh, y, hpre);
+        if (fxh) hpre[1] = -hpre[1];
         if (hin) load_inflow<NV>(g, y, hpre);
         LRec<NV> hr;
         make_lrec<NV>(hpre, ph, hr);
         row_put<NV>(buf, hslot, hr);
         asm volatile("" ::: "memory");  // the prefetch below stays after this use
-        row_load_raw<NV>(a.Uk, g, hxy, y + 1, hpre);
+        row_load_in<NV>(a.Uk, g, hx8, min(y + 1, g.n[1] - 1), hpre);  // (past the chunk: unused)
       }
       __syncthreads();
       __builtin_amdgcn_s_setprio(0);
@@ -281,11 +321,13 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       double Fx[NV];
       const bool mx =
           face_linear_l<NV, 0, SPLIT, HYB>(RowSrc<NV>{buf, lane}, ph, ph.eps_thr[0], lfx, Fx);
-      const long long off = oxy + (long long)y * g.stride[1];
+      const long long row = (long long)y * g.stride[1], off = oxy + row;
       double unp[NV] = {};
       if (OUT == OUT_RK && a.rk_a != 0.0) {
+        const char* p = (const char*)(a.Un + row);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) unp[v] = __builtin_nontemporal_load(&a.Un[v * g.ncell + off]);
+        for (int v = 0; v < NV; ++v)
+          unp[v] = __builtin_nontemporal_load((const double*)(p + v * g.ncell * 8 + cx8));
       }
       // y face y + 1/2: cells y-2, y-1 (ring), y .. y+3 (registers)
       double Fy[NV];
@@ -294,11 +336,11 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
                             ph.eps_thr[1], lfy, Fy);
       double Fr[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Fr[v] = __shfl_down(Fx[v], 1, RW);
-      const int mxr = __shfl_down((int)mx, 1, RW);
+      for (int v = 0; v < NV; ++v) Fr[v] = next_lane(Fx[v]);
+      const int mxr = next_lane_int((int)mx);
       const unsigned cm =
           own ? ((mx ? 1u : 0u) | (mxr ? 2u : 0u) | (yprev ? 4u : 0u) | (ycur ? 8u : 0u)) : 0u;
-      list_append(a, off, cm);
+      list_append(a, lbuf, ln, off, cm);
       yprev = ycur;
       // raised wave priority from the stores through the next row's loads and
       // records to its barrier, normal for the faces (measured 1.6 % faster
@@ -306,16 +348,17 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       __builtin_amdgcn_s_setprio(2);
       if (own) {
         double un[NV];
+        char* p = (char*)(a.out + row);
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           const double dU = ((Fx[v] - Fr[v]) + (Fyp[v] - Fy[v])) * ph.inv_dx60;
           if (OUT == OUT_RK) {
             double r = a.rk_b * (r0.U[v] + dt * dU);
             if (a.rk_a != 0.0) r += a.rk_a * unp[v];
-            __builtin_nontemporal_store(r, &a.out[v * g.ncell + off]);
+            __builtin_nontemporal_store(r, (double*)(p + v * g.ncell * 8 + cx8));
             un[v] = r;
           } else {
-            __builtin_nontemporal_store(dU, &a.out[v * g.ncell + off]);
+            __builtin_nontemporal_store(dU, (double*)(p + v * g.ncell * 8 + cx8));
           }
         }
         if (OUT == OUT_RK && a.cfl != nullptr && cm == 0u)
@@ -329,14 +372,16 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       r0 = r1;
       r1 = r2;
       r2 = r3;
-      row_flip<NV>(g, fx, y + 4, upre);
+      if (fx) upre[1] = -upre[1];
+      if (fyn) upre[2] = -upre[2];
       make_lrec<NV>(upre, ph, r3);
       asm volatile("" ::"v"(r3.U[0]), "v"(r3.U[NV - 1]), "v"(r3.p), "v"(r3.c), "v"(r3.iw)
                    : "memory");
-      row_load_raw<NV>(a.Uk, g, oxy, y + 5, upre);
+      prefetch(y + 5);
       __syncthreads();  // row buffer free for the next row
     }
   }
+  list_flush(a, lbuf, ln);
   if (OUT == OUT_RK && a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
 }
 
@@ -623,6 +668,7 @@ __global__ __launch_bounds__(RW, 2) void row_kernel(RowArgs a, KGrid g, KPhys ph
                                                     int tiles_x) {
   __shared__ double buf[NV + 3][RB];
   __shared__ double ring[2][NV + 3][RW];
+  __shared__ unsigned long long lbuf[LIST_BUF];
   double dt = 0.0;
   if (OUT == OUT_RK) {
     dt = a.clock != nullptr
@@ -634,7 +680,7 @@ __global__ __launch_bounds__(RW, 2) void row_kernel(RowArgs a, KGrid g, KPhys ph
   const int tx = item % tiles_x, ty = item / tiles_x;
   const int y0 = ty * ych;
   const int y1 = min(y0 + ych, g.n[1]);
-  row_item<NV, OUT, SPLIT, HYB>(a, g, ph, buf, ring, tx * RT, y0, y1, dt);
+  row_item<NV, OUT, SPLIT, HYB>(a, g, ph, buf, ring, lbuf, tx * RT, y0, y1, dt);
 }
 
 }  // namespace wl2
