@@ -121,12 +121,12 @@ int weno_l2is_params_default(weno_l2is_params *p, int nx, int ny, int nz,
  * correction list (8 bytes per cell), a 6.4 KB control block (6 KB more for
  * 2D grids with global LF splitting, 12.4 KB for 1D grids), for 2D
  * grids of 131072 cells or more the face-once correction buffers (68 bytes
- * per cell), and for 3D grids a face buffer (120 bytes per cell) where the
- * corrections compute each face once: with every face WENO (LLF
- * splitting), and with the hybrid switch (per field or per face), which
- * also lists the faces that need the WENO flux (12 bytes per cell).  About
- * 4.4 GB for a 256^3 grid with the hybrid switch (4.2 GB with every face
- * WENO, 2.2 GB with every face linear). */
+ * per cell), and for 3D grids the running sums of the directions (80 bytes
+ * per cell) with every face WENO, or with the hybrid switch (per field or
+ * per face) a face buffer (120 bytes per cell) and the lists of the faces
+ * that need the WENO flux (12 bytes per cell).  About 4.4 GB for a 256^3
+ * grid with the hybrid switch (3.5 GB with every face WENO, 2.2 GB with
+ * every face linear). */
 int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma,
                      const weno_l2is_params *p, void *hip_stream,
                      weno_l2is_ctx **out);
@@ -251,7 +251,8 @@ int weno_l2is_status(weno_l2is_ctx *ctx, unsigned *status_bits, int clear);
  * each flagged face once: 2D grids of 131072 cells or more, and 3D grids
  * with every face WENO or the hybrid switch).
  * zchunk: z planes (3D) or rows (2D, at most 62) per work item of the fused
- * kernels (0 = automatic).  waves_per_simd: register budget of the 3D fused
+ * kernels, in 3D with every face WENO the cells that a lane marches through
+ * along y and z (0 = automatic).  waves_per_simd: register budget of the 3D fused
  * kernel, 1 or 2 (0 = default 2).  The sweeps agree with the fused kernels
  * to round-off; the chunk, the register budget and the correction mode
  * change no result bit. */

@@ -294,35 +294,17 @@ bool use_line_steps(const weno_l2is_ctx* c) {
 // extra launch.
 constexpr long long FACE_ONCE_MIN_CELLS = 1ll << 17;
 
-// Rows per work item of the 2D row kernel: the tuned value, else the y of 4
-// .. 20 with the least estimated time.  One wavefront per item and two per
-// SIMD: 2048 items run at once, in rounds of about y + 1.5 rows' time (the
-// 1.5: an item's first window and its first y face); a last round of at most
-// one wavefront per SIMD takes about 0.8 of a full one, one of more a full
-// one.  Measured against a sweep of y (us per step, chosen / 11 rows / best):
-// 1024^2 9 rows 166/174/166, 1200x800 8 rows 158/170/158, 1531x1013 13 rows
-// 206/251/206, 2048^2 17 rows 423/425/423, 3000x1700 20 rows 495/521/495,
-// 4096x1000 17 rows 424/424/424.  Beyond 20 rows an item's tail leaves more
-// of the chip idle than its window costs.
+// Rows per work item of the 2D row kernel: the tuned value, else the balanced
+// one of 2 .. 20.  Measured against a sweep of y (us per step, chosen / 11 rows
+// / best): 1024^2 9 rows 166/174/166, 1200x800 8 rows 158/170/158, 1531x1013 13
+// rows 206/251/206, 2048^2 17 rows 423/425/423, 3000x1700 20 rows 495/521/495,
+// 4096x1000 17 rows 424/424/424.  Beyond 20 rows an item's tail leaves more of
+// the chip idle than its window costs.
 int row_ych(const weno_l2is_ctx* c) {
   if (c->dim == 1) return 1;
   const int cap = ROW_MAX_YCH < c->n[1] ? ROW_MAX_YCH : c->n[1];
   if (c->zchunk > 0) return c->zchunk < cap ? c->zchunk : cap;
-  constexpr long long ROUND = 2048;
-  const long long tiles = (c->n[0] + ROW_TILE - 1) / ROW_TILE;
-  int best = cap < 4 ? cap : 4;
-  long long least = 0;
-  for (int y = best; y <= 20 && y <= cap; ++y) {
-    const long long items = tiles * ((c->n[1] + y - 1) / y);
-    const long long rest = items % ROUND;
-    const long long tenths = items / ROUND * 10 + (rest == 0 ? 0 : rest <= ROUND / 2 ? 8 : 10);
-    const long long cost = tenths * (2 * y + 3);
-    if (least == 0 || cost < least) {
-      least = cost;
-      best = y;
-    }
-  }
-  return best;
+  return balanced_chunk((c->n[0] + ROW_TILE - 1) / ROW_TILE, c->n[1], 2, 20);
 }
 
 // The counters of the next stage launch, clearing both if needed.
@@ -480,8 +462,13 @@ hipError_t launch_fused(const weno_l2is_ctx* c, int out_kind, const double* Uk, 
   L.g = c->g;
   L.ph = c->ph;
   L.stream = c->stream;
+  L.march = c->zchunk;
   hipError_t e = turn.reset ? fused3d_reset(L) : hipSuccess;
   if (e != hipSuccess) return turn.done(e);
+  if (L.fo3 != nullptr && c->p.hybrid == WL2_HYB_WENO_ONLY) {
+    TimedLaunch tl(c, out_kind == OUT_RK ? "weno3d_rk" : "weno3d_rhs");
+    return turn.done(weno3d_stage(L));
+  }
   {
     TimedLaunch tl(c, out_kind == OUT_RK ? "fused3d_rk" : "fused3d_rhs");
     if ((e = fused3d_main(L)) != hipSuccess) return turn.done(e);
@@ -661,12 +648,15 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
          hipMalloc(&c->fo_map, sizeof(unsigned int) * (size_t)c->ncell) == hipSuccess &&
          // every map value stays a valid entry index (< ncell) from the start
          hipMemsetAsync(c->fo_map, 0, sizeof(unsigned int) * (size_t)c->ncell, c->stream) == hipSuccess;
-  // 3D: the corrections compute each face once into a face buffer (15
-  // doubles per cell): every face with every face WENO (LLF splitting), the
-  // faces of the face lists (3 entries per cell) with the hybrid switch
+  // 3D: with every face WENO the running sums of the
+  // directions (10 doubles per cell); with the hybrid switch the corrections
+  // compute each face once into a face buffer (15 doubles per cell), located
+  // by face lists (3 entries per cell)
   const bool hyb3 = c->dim == 3 && (p->hybrid == WL2_HYB_PER_FIELD || p->hybrid == WL2_HYB_PER_FACE);
-  if (ok && c->dim == 3 && ((p->hybrid == WL2_HYB_WENO_ONLY && p->split == WL2_SPLIT_LLF) || hyb3))
-    ok = hipMalloc(&c->fo3, sizeof(double) * fused3d_face_doubles(c->n)) == hipSuccess;
+  const bool weno3 = c->dim == 3 && p->hybrid == WL2_HYB_WENO_ONLY && nx <= WENO3D_MAX_NX;
+  if (ok && (weno3 || hyb3))
+    ok = hipMalloc(&c->fo3, sizeof(double) * (weno3 ? 10 * (size_t)c->ncell : fused3d_face_doubles(c->n))) ==
+         hipSuccess;
   if (ok && hyb3)
     ok = hipMalloc(&c->flist, sizeof(unsigned int) * fused3d_flist_entries(c->n)) == hipSuccess;
   if (ok && c->dim == 2 && p->split == WL2_SPLIT_LF)

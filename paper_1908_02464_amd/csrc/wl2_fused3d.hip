@@ -85,30 +85,6 @@ size_t fused3d_face_doubles(const int n[3]) {
   return 5 * ((nx + 1) * ny * nz + nx * (ny + 1) * nz + nx * ny * (nz + 1));
 }
 
-// Every face WENO with a face buffer: each face's change once (three
-// launches, one per direction), then the per-cell sums.
-template <int O, int W>
-static hipError_t fix_face_once(const FusedLaunch& L, const FusedArgs& a) {
-  const long long nx = L.n[0], ny = L.n[1], nz = L.n[2];
-  const long long nfx = (nx + 1) * ny * nz, nfy = nx * (ny + 1) * nz, nfz = nx * ny * (nz + 1);
-  double* Dx = L.fo3;
-  double* Dy = Dx + 5 * nfx;
-  double* Dz = Dy + 5 * nfy;
-  const auto blocks = [](long long n, int t) {
-    const long long b = (n + t - 1) / t;
-    return dim3((unsigned)(b < (1ll << 20) ? b : (1ll << 20)));
-  };
-  hipLaunchKernelGGL((weno_face3d_kernel<O, 0, SPLIT_LLF, HYB_WENO_ONLY, W>), blocks(nfx, 128), dim3(128), 0,
-                     L.stream, a, L.g, L.ph, Dx);
-  hipLaunchKernelGGL((weno_face3d_kernel<O, 1, SPLIT_LLF, HYB_WENO_ONLY, W>), blocks(nfy, 128), dim3(128), 0,
-                     L.stream, a, L.g, L.ph, Dy);
-  hipLaunchKernelGGL((weno_face3d_kernel<O, 2, SPLIT_LLF, HYB_WENO_ONLY, W>), blocks(nfz, 128), dim3(128), 0,
-                     L.stream, a, L.g, L.ph, Dz);
-  hipLaunchKernelGGL((weno_sum3d_kernel<O>), blocks(nx * ny * nz, 256), dim3(256), 0, L.stream, a, L.g,
-                     L.ph, Dx, Dy, Dz);
-  return hipGetLastError();
-}
-
 // Face lists: the offsets of both lists (one small launch), each listed
 // face's change once into the face buffer (one launch for the three lists),
 // then the listed cells' sums.
@@ -130,19 +106,14 @@ static hipError_t fix_face_lists(const FusedLaunch& L, const FusedArgs& a) {
 
 // The correction kernels have builds for the weighting of Eq.(28) fixed at
 // compile time; the comparison weightings take builds that read it at run
-// time.  (A run-time choice keeps the values of all three in registers: the
-// every-face-WENO face kernel then needs more than 256 VGPRs and runs one
-// wave per SIMD, 1.6 against 1.2 ms per launch at 256^3.)
+// time, except with every face WENO, where it is most of the work (a choice at
+// run time keeps the values of all three in registers).
 hipError_t fused3d_fix(const FusedLaunch& L) {
   const FusedArgs a = make_args(L);
   const dim3 fg(1024), fb(128);
   const int sp = L.ph.split, hy = L.ph.hybrid;
   const bool w0 = L.ph.weights == W_L2IS;
-  if (L.fo3 != nullptr && sp == SPLIT_LLF && hy == HYB_WENO_ONLY) {
-    if (L.out_kind == OUT_RK) return w0 ? fix_face_once<OUT_RK, W_L2IS>(L, a) : fix_face_once<OUT_RK, -1>(L, a);
-    return w0 ? fix_face_once<OUT_WRITE, W_L2IS>(L, a) : fix_face_once<OUT_WRITE, -1>(L, a);
-  }
-  if (L.fo3 != nullptr && L.flist != nullptr && hy != HYB_WENO_ONLY)
+  if (L.fo3 != nullptr && L.flist != nullptr)
     return L.out_kind == OUT_RK ? fix_face_lists<OUT_RK>(L, a) : fix_face_lists<OUT_WRITE>(L, a);
   if (!(sp == SPLIT_LLF && hy == HYB_WENO_ONLY)) {
     // offsets of the per-workgroup list regions (the dense form needs none;
@@ -160,7 +131,8 @@ hipError_t fused3d_fix(const FusedLaunch& L) {
   do {                                                                                      \
     if (w0 && sp == SPLIT_LLF && hy == HYB_PER_FIELD) WL2_FIX(O, SPLIT_LLF, HYB_PER_FIELD, W_L2IS); \
     else if (w0 && sp == SPLIT_LLF && hy == HYB_WENO_ONLY) WL2_FIX(O, SPLIT_LLF, HYB_WENO_ONLY, W_L2IS); \
-    else if (sp == SPLIT_LLF && hy == HYB_WENO_ONLY) WL2_FIX(O, SPLIT_LLF, HYB_WENO_ONLY, -1);  \
+    else if (sp == SPLIT_LLF && hy == HYB_WENO_ONLY && L.ph.weights == W_IS) WL2_FIX(O, SPLIT_LLF, HYB_WENO_ONLY, W_IS); \
+    else if (sp == SPLIT_LLF && hy == HYB_WENO_ONLY) WL2_FIX(O, SPLIT_LLF, HYB_WENO_ONLY, W_IS_B01); \
     else if (w0 && sp == SPLIT_ROE && hy == HYB_PER_FIELD) WL2_FIX(O, SPLIT_ROE, HYB_PER_FIELD, W_L2IS); \
     else WL2_FIX(O, -1, -1, -1);                                                            \
   } while (0)

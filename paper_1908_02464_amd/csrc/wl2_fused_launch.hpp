@@ -27,9 +27,11 @@ struct FusedLaunch {
   int out_kind;  // OUT_WRITE or OUT_RK
   int zc;        // z planes per workgroup
   int wpe;       // 1 or 2 waves per SIMD
-  double* fo3;   // face changes of the x, y, z faces, 5 values each (face-once
-                 // corrections: every face WENO, or the face lists), or null:
-                 // the per-cell kernel
+  double* fo3;   // face changes of the x, y, z faces, 5 values each (face
+                 // lists), or with every face WENO the 10 running sums per
+                 // cell (weno3d_stage), or null: the per-cell kernel
+  int march;     // weno3d_stage: cells a lane marches through along y and z (0:
+                 // chosen from the grid)
   unsigned int* flist;        // face lists (fused3d_flist_entries of them), or null
   unsigned int* counts_f;     // faces each workgroup listed, per direction
   unsigned int* offs_f;       // their exclusive prefix sums (one more entry)
@@ -46,7 +48,33 @@ struct FusedLaunch {
 hipError_t fused3d_reset(const FusedLaunch& L);
 hipError_t fused3d_main(const FusedLaunch& L);
 hipError_t fused3d_fix(const FusedLaunch& L);
-// Doubles of the face buffer (FusedLaunch::fo3) of an n[0] x n[1] x n[2] grid.
+// A whole stage with every face WENO and fo3 given (three
+// launches; the list of this stage stays empty and the next one's counter is
+// cleared).
+hipError_t weno3d_stage(const FusedLaunch& L);
+constexpr int WENO3D_MAX_NX = 1 << 27;  // two rows within a 32-bit byte offset
+// Cells per lane of a kernel that marches wavefronts of columns (`waves` of
+// them) along n cells: of lo .. hi the length with the least estimated time.
+// Two wavefronts per SIMD run at once, 2048, in rounds of about len + 1.5
+// cells' time (the 1.5: a chunk's first stencil and its first face); a last
+// round of at most one wavefront per SIMD takes about 0.8 of a full one.
+inline int balanced_chunk(long long waves, int n, int lo, int hi) {
+  constexpr long long ROUND = 2048;
+  int best = n < lo ? n : lo;
+  long long least = 0;
+  for (int len = best; len <= hi && len <= n; ++len) {
+    const long long items = waves * ((n + len - 1) / len);
+    const long long rest = items % ROUND;
+    const long long tenths = items / ROUND * 10 + (rest == 0 ? 0 : rest <= ROUND / 2 ? 8 : 10);
+    const long long cost = tenths * (2 * len + 3);
+    if (least == 0 || cost < least) {
+      least = cost;
+      best = len;
+    }
+  }
+  return best;
+}
+// Doubles of the face buffer (FusedLaunch::fo3) for the face lists of an n[0] x n[1] x n[2] grid.
 size_t fused3d_face_doubles(const int n[3]);
 // Entries of the per-workgroup count array (FusedLaunch::counts): enough for
 // any z chunk (one workgroup per column tile and plane at most).

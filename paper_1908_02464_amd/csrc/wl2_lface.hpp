@@ -395,14 +395,19 @@ __device__ __forceinline__ void left_row_rt(const Roe<NV>& s, int k, double (&r)
 }
 
 // The change of the face's flux for the fields in mask: R f - F60 / 60.
-template <int NV, int DIR, int W = -1, class Src>
+// `early` runs before the last field (a kernel's loads for what follows).
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int NV, int DIR, int W = -1, class Src, class Hook = NoHook>
 __device__ __forceinline__ void lean_correction(const Src& src, unsigned mask, const FaceState<NV>& st,
                                                 const double (&F60)[NV], const KPhys& ph,
-                                                double (&dF)[NV]) {
+                                                double (&dF)[NV], const Hook& early = Hook()) {
   double LF[NV], f[NV];
   project<NV, DIR>(st.s, st.Fc6, LF);
 #define WL2_LF(K)                                                                                 \
   if constexpr (K < NV) {                                                                         \
+    if constexpr (K == NV - 1) early();                                                           \
     f[K] = ((mask >> K) & 1u) ? lean_field<NV, DIR, K, W>(src, st.s, st.a[K], st.dv[K], ph)       \
                               : LF[K] + st.a[K] * st.dv[K];                                       \
   }
