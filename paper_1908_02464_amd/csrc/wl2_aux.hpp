@@ -267,21 +267,25 @@ __global__ __launch_bounds__(RED_BLOCK) void lf_reduce_kernel(const double* __re
 
 // The maximum over the slots into lf_bits (|u - c| for field 0, |u| for the
 // entropy and shear fields, |u + c| for field nv - 1; directions beyond the
-// grid's get 0) and the slots cleared for the next reduction.  One wave.
+// grid's get 0) and the slots cleared for the next reduction.  One wave, a
+// lane per slot.
 [[maybe_unused]] static __global__ void lf_finalize_kernel(StepCtl* ctl, int nv) {
+  static_assert(LF_SLOTS <= 64, "one slot per lane");
   const int t = threadIdx.x;
-  if (t < 9) {
-    const int d = t / 3, j = t % 3;
-    unsigned long long m = 0ull;
-    for (int s = 0; s < LF_SLOTS; ++s) {
-      const unsigned long long b = ctl->lf_slots[s].bits[d][j];
-      m = b > m ? b : m;
-      ctl->lf_slots[s].bits[d][j] = 0ull;
+  LfSlot s{};
+  if (t < LF_SLOTS) {
+    s = ctl->lf_slots[t];
+    ctl->lf_slots[t] = LfSlot{};
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const unsigned long long m =
+          (unsigned long long)__double_as_longlong(wave_max(__longlong_as_double((long long)s.bits[d][j])));
+      const int k = j == 0 ? 0 : j == 2 ? nv - 1 : t;  // lanes 1 .. nv - 2 for the fields between
+      if (j == 1 ? t > 0 && t < nv - 1 : t == 0) ctl->lf_bits[d][k] = m;
     }
-    if (j == 0) ctl->lf_bits[d][0] = m;
-    else if (j == 2) ctl->lf_bits[d][nv - 1] = m;
-    else
-      for (int k = 1; k < nv - 1; ++k) ctl->lf_bits[d][k] = m;
   }
 }
 

@@ -335,7 +335,7 @@ struct StageTurn {
   bool fold_cfl = false;  // fold the CFL maximum of the output (next step's dt)
   bool kclock = false;    // 1D/2D stage 1: the stage kernel forms the step's dt
   bool commit = false;    // the stage after it: the tile kernel commits the clock
-  // tile kernel with LF splitting inside advance: index of the stage in the
+  // 2D with LF splitting inside advance: index of the stage in the
   // call (its speeds were folded by the stage before, from the second on), and
   // whether a further one follows; -1: the speeds are reduced separately
   int lf = -1;
@@ -504,6 +504,7 @@ hipError_t stage(const weno_l2is_ctx* c, const double* Uk, const double* Un, dou
   const double tg = t.kclock ? -1.0 : tc;  // -1: the clock's t
   if (c->p.split == WL2_SPLIT_LF) {
     if (t.lf <= 0) e = launch_lf(c, Uk, tg);
+    else if (!use_tile(c)) e = fill_yghosts(c, Uk, tg);
   } else if (!use_tile(c)) {
     e = fill_yghosts(c, Uk, tg);
   }
@@ -521,7 +522,7 @@ hipError_t stage(const weno_l2is_ctx* c, const double* Uk, const double* Un, dou
 // One step; `step` of `n_steps` of an advance call (-1: a step by itself).
 hipError_t rk3(const weno_l2is_ctx* c, double* U, int step = -1, int n_steps = 0) {
   const bool in_call = step >= 0, more = step + 1 < n_steps;
-  const bool lf = in_call && c->lfs != nullptr && c->p.split == WL2_SPLIT_LF && use_tile(c);
+  const bool lf = in_call && c->lfs != nullptr && c->p.split == WL2_SPLIT_LF && use_row(c);
   StageTurn t[3];
   t[0].kclock = in_call && step > 0 && use_row(c);
   t[1].commit = t[0].kclock;

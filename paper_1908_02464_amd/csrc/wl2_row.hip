@@ -37,7 +37,7 @@ hipError_t row_fix(const RowLaunch& L) {
   const RowArgs a{L.Uk,   L.out,    L.Un, L.ctl,        L.rk_a,
                   L.rk_b, L.list,   L.list_n, L.list_clear,
                   L.out_kind == OUT_RK ? L.cfl : nullptr, L.out_kind == OUT_RK ? L.clock : nullptr,
-                  L.cfl_dx, L.s_floor};
+                  L.cfl_dx, L.s_floor, L.lf_in, L.lf_out, L.lf_clear};
   const dim3 fg(1024), fb(128);
   // the per-cell kernel: 2048 workgroups, so that lists of up to 16384
   // cells take its field-parallel mode (workgroups past the list's end
@@ -88,7 +88,7 @@ hipError_t row_launch(const RowLaunch& L) {
   const RowArgs a{L.Uk,   L.out,  L.Un,     L.ctl, L.rk_a,
                   L.rk_b, L.list, L.list_n, nullptr,
                   L.out_kind == OUT_RK ? L.cfl : nullptr, L.out_kind == OUT_RK ? L.clock : nullptr,
-                  L.cfl_dx, L.s_floor};
+                  L.cfl_dx, L.s_floor, L.lf_in, L.lf_out, L.lf_clear};
   const int tiles_x = (L.g.n[0] + RT - 1) / RT;
   const int ych = L.nvar == 3 ? 1 : (L.ych < 1 ? 1 : (L.ych > ROW_MAX_YCH ? ROW_MAX_YCH : L.ych));
   const long long chunks = L.nvar == 3 ? 1 : (L.g.n[1] + ych - 1) / ych;

@@ -18,6 +18,7 @@
 // the halo is prefetched a row ahead, with the sign flip of mirror ghosts
 // applied at use.
 #pragma once
+#include "wl2_aux.hpp"
 #include "wl2_lface.hpp"
 #include "wl2_wface.hpp"
 
@@ -31,7 +32,7 @@ struct RowArgs {
   const double* Uk;    // stage input
   double* out;         // RK: U^(k+1); WRITE: dU/dt
   const double* Un;    // RK: U^n (read when rk_a != 0)
-  const StepCtl* ctl;  // dt and the global LF speeds
+  StepCtl* ctl;        // dt and the global LF speeds
   double rk_a, rk_b;   // RK: out = rk_a U^n + rk_b (Uk + dt dU)
   unsigned long long* list;  // cells next to a face that needs the WENO flux
   unsigned int* list_n;      // entries in list
@@ -45,7 +46,37 @@ struct RowArgs {
                              // inflow speed floor s_floor) and its correction
                              // kernel commits the clock (clock_commit); else null
   double cfl_dx, s_floor;
+  // LF splitting within a call of several stages: the speeds that the stage
+  // before folded (null: ctl->lf_bits holds them), where those of the output are
+  // folded (or null), and the set to clear for the next stage.  Against a
+  // reduction pass and its finalisation per stage (14.5 + 4.6 us at 1531x1013):
+  // 238 -> 212 us per step
+  const LfSlot* lf_in;
+  LfSlot* lf_out;
+  LfSlot* lf_clear;
 };
+
+// What a kernel folds from the cells that it finishes: the CFL speed (a.cfl)
+// and, in builds that may split globally, the LF speeds (a.lf_out).
+template <int NV, bool LF>
+struct CellFold {
+  double cfl_max = 0.0, mx[LF ? NV - 2 : 1][3] = {};
+  bool cfl_bad = false;
+  __device__ __forceinline__ void cell(const RowArgs& a, const KPhys& ph, const double (&un)[NV]) {
+    if (a.cfl != nullptr) cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
+    if constexpr (LF) {
+      if (a.lf_out != nullptr) lf_fold_cell<NV>(un, ph.gamma, mx);
+    }
+  }
+  __device__ __forceinline__ void commit(const RowArgs& a) {
+    if (a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
+    if constexpr (LF) {
+      if (a.lf_out != nullptr) lf_commit_wave<NV - 2>(a.lf_out, mx);
+    }
+  }
+};
+template <int NV, int OUT, int SPLIT>
+constexpr bool folds_lf() { return NV == 4 && OUT == OUT_RK && (SPLIT < 0 || SPLIT == SPLIT_LF); }
 
 // Entry of the correction list: element offset << 8 | face mask (bit 0 x-, 1
 // x+, 2 y-, 3 y+).  A wavefront collects its entries in LDS (buf, n of them)
@@ -181,8 +212,28 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
                                          unsigned long long* lbuf, int x0, int y0, int y1, double dt) {
   int ln = 0;  // entries in lbuf
   const int lane = threadIdx.x & (RW - 1);
-  const unsigned long long* lfx = a.ctl->lf_bits[0];
-  const unsigned long long* lfy = a.ctl->lf_bits[1];
+  // global LF speeds, x and y (read only by LF builds)
+  unsigned long long lfx[NV], lfy[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    lfx[k] = a.ctl->lf_bits[0][k];
+    lfy[k] = a.ctl->lf_bits[1][k];
+  }
+  constexpr bool LF = folds_lf<NV, OUT, SPLIT>();
+  if constexpr (LF) {
+    if (a.lf_in != nullptr) {
+      lf_take_wave<NV>(a.lf_in, 0, lfx);
+      lf_take_wave<NV>(a.lf_in, 1, lfy);
+      if (blockIdx.x == 0 && lane < LF_SLOTS) a.lf_clear[lane] = LfSlot{};
+      if (blockIdx.x == 0 && lane == 0) {  // for the correction kernels
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+          a.ctl->lf_bits[0][k] = lfx[k];
+          a.ctl->lf_bits[1][k] = lfy[k];
+        }
+      }
+    }
+  }
   // the lane's column (a ghost or the next item's column for lane RT and past
   // the grid edge: those fill the row buffer but own no cell)
   bool fx;
@@ -199,8 +250,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
   const long long oxy = cx;  // row 0 element offset of the column (x stride 1)
   const long long hxy = hx;
   const unsigned cx8 = (unsigned)cx * 8u, hx8 = (unsigned)hx * 8u;
-  double cfl_max = 0.0;  // CFL speed of the cells written here (a.cfl set)
-  bool cfl_bad = false;
+  CellFold<NV, LF> fold;  // of the cells written here
 
   if constexpr (NV == 3) {
     // 1D: one row
@@ -250,8 +300,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
       }
       // a listed cell is finished (and its CFL speed counted) by the
       // correction kernel
-      if (OUT == OUT_RK && a.cfl != nullptr && cm == 0u)
-        cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
+      if (OUT == OUT_RK && cm == 0u) fold.cell(a, ph, un);
     }
     __syncthreads();  // the buffer is reused by the next item
   } else {
@@ -361,8 +410,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
             __builtin_nontemporal_store(dU, (double*)(p + v * g.ncell * 8 + cx8));
           }
         }
-        if (OUT == OUT_RK && a.cfl != nullptr && cm == 0u)
-          cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
+        if (OUT == OUT_RK && cm == 0u) fold.cell(a, ph, un);
       }
 #pragma unroll
       for (int v = 0; v < NV; ++v) Fyp[v] = Fy[v];
@@ -382,7 +430,7 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
     }
   }
   list_flush(a, lbuf, ln);
-  if (OUT == OUT_RK && a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
+  if (OUT == OUT_RK) fold.commit(a);
 }
 
 // Nonlinear part of the flux of the flagged faces of one listed cell at
@@ -422,8 +470,8 @@ constexpr int fix_fields_cells() { return NV == 4 ? 8 : 16; }
 // y+ as serial_correction sums them: the same bits.
 template <int NV, int OUT, int SPLIT, int HYB>
 __device__ __forceinline__ void row_fix_fields(const RowArgs& a, const KGrid& g, const KPhys& ph,
-                                               unsigned int n, double scale, double& cfl_max,
-                                               bool& cfl_bad) {
+                                               unsigned int n, double scale,
+                                               CellFold<NV, folds_lf<NV, OUT, SPLIT>()>& fold) {
   constexpr int NF = 2 * (NV - 2);
   constexpr int CPB = fix_fields_cells<NV>();
   __shared__ double sdf[CPB][NF][NV];
@@ -480,7 +528,7 @@ __device__ __forceinline__ void row_fix_fields(const RowArgs& a, const KGrid& g,
         un[v] = a.out[v * g.ncell + c] + scale * (acc[v] * ph.inv_dx);
         a.out[v * g.ncell + c] = un[v];
       }
-      if (OUT == OUT_RK && a.cfl != nullptr) cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
+      if (OUT == OUT_RK) fold.cell(a, ph, un);
     }
     __syncthreads();  // sdf is free for the next round
   }
@@ -504,21 +552,19 @@ __global__ __launch_bounds__(128) void row_fix_kernel(RowArgs a, KGrid g, KPhys 
   const unsigned int n = *a.list_n;
   const unsigned int threads = gridDim.x * blockDim.x;
   const unsigned int tid = blockIdx.x * blockDim.x + threadIdx.x;
-  double cfl_max = 0.0;
-  bool cfl_bad = false;
+  CellFold<NV, folds_lf<NV, OUT, SPLIT>()> fold;
   if ((unsigned long long)n <= (unsigned long long)gridDim.x * fix_fields_cells<NV>()) {
-    row_fix_fields<NV, OUT, SPLIT, HYB>(a, g, ph, n, scale, cfl_max, cfl_bad);
+    row_fix_fields<NV, OUT, SPLIT, HYB>(a, g, ph, n, scale, fold);
   } else {
     for (unsigned int i = tid; i < n; i += threads) {
       const unsigned long long e = a.list[i];
       double un[NV];
       row_fix_cell<NV, SPLIT, HYB>(a.Uk, a.out, a.ctl, g, ph, (long long)((e >> 8) & 0xffffffffull),
                                    (unsigned)(e & 0xffu), scale, un);
-      if (OUT == OUT_RK && a.cfl != nullptr)
-        cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
+      if (OUT == OUT_RK) fold.cell(a, ph, un);
     }
   }
-  if (OUT == OUT_RK && a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
+  if (OUT == OUT_RK) fold.commit(a);
 }
 
 // Face-once corrections of a long list (single grid).  Every flagged face
@@ -608,8 +654,7 @@ __global__ __launch_bounds__(128) void row_sum_kernel(RowArgs a, KGrid g, KPhys 
   constexpr int ND = NV - 2;
   const unsigned int n = *a.list_n;
   const unsigned int threads = gridDim.x * blockDim.x;
-  double cfl_max = 0.0;
-  bool cfl_bad = false;
+  CellFold<NV, folds_lf<NV, OUT, SPLIT>()> fold;
   for (unsigned int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += threads) {
     const unsigned long long e = a.list[k];
     const long long off = (long long)((e >> 8) & 0xffffffffull);
@@ -652,10 +697,9 @@ __global__ __launch_bounds__(128) void row_sum_kernel(RowArgs a, KGrid g, KPhys 
       un[v] = a.out[v * g.ncell + off] + scale * (acc[v] * ph.inv_dx);
       a.out[v * g.ncell + off] = un[v];
     }
-    if (OUT == OUT_RK && a.cfl != nullptr)
-      cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
+    if (OUT == OUT_RK) fold.cell(a, ph, un);
   }
-  if (OUT == OUT_RK && a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
+  if (OUT == OUT_RK) fold.commit(a);
 }
 
 [[maybe_unused]] static __global__ void row_list_reset_kernel(unsigned int* n) {

@@ -15,7 +15,7 @@ struct RowLaunch {
   const double* Uk;
   double* out;
   const double* Un;
-  const StepCtl* ctl;
+  StepCtl* ctl;
   double rk_a, rk_b;
   int out_kind;  // OUT_WRITE or OUT_RK
   int ych;       // rows per work item (2D)
@@ -30,13 +30,13 @@ struct RowLaunch {
   StepCtl* clock;            // RK stage 1: the stage kernel forms the step's dt
                              // from the CFL maximum folded here (or null)
   double cfl_dx, s_floor;    // with clock: CFL number x dx, inflow speed floor
+  const LfSlot* lf_in;       // LF splitting: speeds of the input (null: ctl->lf_bits),
+  LfSlot* lf_out;            // where the output's are folded (or null),
+  LfSlot* lf_clear;          // and the set to clear for the next stage (or null)
   // tile kernel only
   StepCtl* commit;           // stage 2: commit the clock that stage 1 formed (or null)
   const YGhostRule* rule;    // state ghosts of the y sides (or null: none)
   double dx, tc;             // with them: cell size and stage time (yghost_time)
-  const LfSlot* lf_in;       // LF splitting: speeds of the input (null: ctl->lf_bits),
-  LfSlot* lf_out;            // where the output's are folded (or null),
-  LfSlot* lf_clear;          // and the set to clear for the next stage (or null)
   // face-once corrections (2D, long lists): per-entry face changes
   // [2][nvar][fo_cap] and the cell -> entry map [ncell]; null: per cell
   double* fo_D;

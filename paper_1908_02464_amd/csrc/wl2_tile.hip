@@ -20,9 +20,9 @@ hipError_t tile2d_launch(const RowLaunch& L, int rows) {
     a.cfl = L.cfl;
     a.clock = L.clock;
     ta.commit = L.commit;
-    ta.lf_in = L.lf_in;
-    ta.lf_out = L.lf_out;
-    ta.lf_clear = L.lf_clear;
+    a.lf_in = L.lf_in;
+    a.lf_out = L.lf_out;
+    a.lf_clear = L.lf_clear;
   }
   a.cfl_dx = L.cfl_dx;
   a.s_floor = L.s_floor;

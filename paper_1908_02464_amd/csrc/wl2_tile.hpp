@@ -29,9 +29,6 @@ struct TileArgs {
   int yghosts;         // the grid has y state sides (rule)
   YGhostRule rule;
   double dx, tc;       // cell size; time of this stage's ghosts (yghost_time)
-  const LfSlot* lf_in; // LF splitting: the speeds of the input (null: ctl->lf_bits),
-  LfSlot* lf_out;      // where those of the output are folded (or null), and the
-  LfSlot* lf_clear;    // set that the stage before read, cleared for the next one
 };
 
 template <int R>
@@ -110,13 +107,13 @@ __device__ __forceinline__ void tile2d_item(const TileArgs& ta, const KGrid& g, 
   unsigned long long lf[NV] = {};
   if (SPLIT == SPLIT_LF || (SPLIT < 0 && ph.split == SPLIT_LF)) {
     const int d = wave < R ? 0 : 1;
-    if (ta.lf_in != nullptr) {
-      lf_take_wave<NV>(ta.lf_in, d, lf);
+    if (a.lf_in != nullptr) {
+      lf_take_wave<NV>(a.lf_in, d, lf);
     } else {
 #pragma unroll
       for (int k = 0; k < NV; ++k) lf[k] = a.ctl->lf_bits[d][k];
     }
-    if (ta.lf_clear != nullptr && lead && threadIdx.x < LF_SLOTS) ta.lf_clear[threadIdx.x] = LfSlot{};
+    if (a.lf_clear != nullptr && lead && threadIdx.x < LF_SLOTS) a.lf_clear[threadIdx.x] = LfSlot{};
   }
   // U^n of the cell this lane updates
   const int uy = y0 + wave;
@@ -208,10 +205,10 @@ __device__ __forceinline__ void tile2d_item(const TileArgs& ta, const KGrid& g, 
       un[v] = r;
     }
     if (OUT == OUT_RK && a.cfl != nullptr) cfl_max = nan_max(cfl_max, cfl_speed_u<NV>(un, ph.gamma, cfl_bad));
-    if (OUT == OUT_RK && ta.lf_out != nullptr) lf_fold_cell<NV>(un, ph.gamma, mx);
+    if (OUT == OUT_RK && a.lf_out != nullptr) lf_fold_cell<NV>(un, ph.gamma, mx);
   }
   if (OUT == OUT_RK && wave < rows) {
-    if (ta.lf_out != nullptr) lf_commit_wave<NV - 2>(ta.lf_out, mx);
+    if (a.lf_out != nullptr) lf_commit_wave<NV - 2>(a.lf_out, mx);
     if (a.cfl != nullptr) cfl_commit_wave(a.cfl, cfl_max, cfl_bad);
   }
 }

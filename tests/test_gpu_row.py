@@ -38,3 +38,30 @@ def test_rows_per_item_bitwise(nx, ny, kw):
         assert np.array_equal(r[0], res[0][0])
         assert np.array_equal(r[1], res[0][1])
         assert r[2] == res[0][2]
+
+
+# global LF: the speeds folded by the stage before (row kernel and its
+# corrections: face once from 131072 cells, else per cell) against one step per
+# call, which reduces them from the state
+@pytest.mark.parametrize("nx,ny,rows,hybrid", [(130, 67, 5, 0), (400, 350, 7, 0), (400, 350, 7, 2), (900, 760, 0, 0)])
+def test_row_folded_lf_speeds(nx, ny, rows, hybrid):
+    import torch
+    from paper_1908_02464_amd import capi
+    say(f"[row] LF {nx}x{ny} rows={rows} hybrid={hybrid}")
+    U, dx, _ = w.four_quadrant_2d(nx, ny, nx)
+    res = []
+    for one_call in (True, False):
+        p = capi.params_default(nx, ny, 1, dx, bc=[1, 1, 0, 0, 1, 1], split=1, hybrid=hybrid)
+        ctx = capi.Context(nx, ny, 1, dx, 1.4, p)
+        ctx.tune(zchunk=rows)
+        A = to_dev(U)
+        if one_call:
+            ctx.advance(A, 4, 1e300)
+        else:
+            for _ in range(4):
+                ctx.step(A)
+        torch.cuda.synchronize()
+        assert ctx.status() == 0
+        res.append(to_host(A))
+        ctx.close()
+    assert np.array_equal(res[0], res[1])
