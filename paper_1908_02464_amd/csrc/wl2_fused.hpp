@@ -821,46 +821,61 @@ __global__ __launch_bounds__(256) void weno_sumlist3d_kernel(FusedArgs a, KGrid 
 
 // Exclusive prefix sums of the per-workgroup list counts: offs[r] = entries
 // of the regions before r, offs[nreg] = all entries.  One workgroup of 1024
-// threads, each summing a contiguous run of counts.
-__device__ __forceinline__ void scan_counts(const unsigned int* counts, int nreg, unsigned int* offs,
-                                            unsigned int* part) {
-  const int t = threadIdx.x;
+// threads, each summing a contiguous run of counts (eight loads in flight);
+// the runs' sums are scanned within the wavefronts and over their totals.
+// Latency-bound: 224 x 175 x 144, 2688 regions, 17.9 us with a scan over the
+// 1024 sums through LDS, one load at a time and both arrays in one workgroup.
+__device__ __forceinline__ void scan_counts(const unsigned int* __restrict__ counts, int nreg,
+                                            unsigned int* __restrict__ offs) {
+  __shared__ unsigned int part[16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int per = (nreg + 1023) / 1024;
-  const int b = t * per, e = min(b + per, nreg);
+  const int b = min(t * per, nreg), e = min(b + per, nreg);
+  constexpr int K = 8;
   unsigned int sum = 0u;
-  for (int r = b; r < e; ++r) sum += counts[r];
-  part[t] = sum;
+  for (int r = b; r < e; r += K) {
+    unsigned int v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = r + k < e ? counts[r + k] : 0u;
+#pragma unroll
+    for (int k = 0; k < K; ++k) sum += v[k];
+  }
+  unsigned int run = sum;  // inclusive scan over the wavefront
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned int v = __shfl_up(run, d, 64);
+    if (lane >= d) run += v;
+  }
+  if (lane == 63) part[wave] = run;
   __syncthreads();
-  // inclusive scan of the 1024 partial sums (Hillis-Steele)
-  for (int d = 1; d < 1024; d <<= 1) {
-    const unsigned int v = t >= d ? part[t - d] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  run -= sum;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) run += w < wave ? part[w] : 0u;
+  for (int r = b; r < e; r += K) {
+    unsigned int v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = r + k < e ? counts[r + k] : 0u;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (r + k < e) offs[r + k] = run;
+      run += v[k];
+    }
   }
-  unsigned int run = t > 0 ? part[t - 1] : 0u;
-  for (int r = b; r < e; ++r) {
-    offs[r] = run;
-    run += counts[r];
-  }
-  if (t == 1023) offs[nreg] = part[1023];
+  if (t == 1023) offs[nreg] = run;  // (the last thread's run ends the counts, or is empty)
 }
 
 static __global__ __launch_bounds__(1024) void list_scan_kernel(const unsigned int* counts, int nreg,
                                                                 unsigned int* offs) {
-  __shared__ unsigned int part[1024];
-  scan_counts(counts, nreg, offs, part);
+  scan_counts(counts, nreg, offs);
 }
 
-// Both offset arrays of the face-list corrections (cells: counts -> offs;
-// faces: counts_f -> offs_f over the 3 nreg (direction, region) segments) in
-// one launch; nothing to do when the stage listed no cell.
+// Both offset arrays of the face-list corrections, a workgroup each (cells:
+// counts -> offs; faces: counts_f -> offs_f over the 3 nreg (direction,
+// region) segments); nothing to do when the stage listed no cell.
 static __global__ __launch_bounds__(1024) void list_scan2_kernel(FusedArgs a, int nreg) {
-  __shared__ unsigned int part[1024];
   if (*a.list_n == 0u) return;
-  scan_counts(a.counts, nreg, a.offs, part);
-  __syncthreads();
-  scan_counts(a.counts_f, 3 * nreg, a.offs_f, part);
+  if (blockIdx.x == 0) scan_counts(a.counts, nreg, a.offs);
+  else scan_counts(a.counts_f, 3 * nreg, a.offs_f);
 }
 
 [[maybe_unused]] static __global__ void reset_list_kernel(unsigned int* list_n) {

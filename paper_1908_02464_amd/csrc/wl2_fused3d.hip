@@ -93,7 +93,7 @@ static hipError_t fix_face_lists(const FusedLaunch& L, const FusedArgs& a) {
   const int sp = L.ph.split, hy = L.ph.hybrid;
   const bool w0 = L.ph.weights == W_L2IS;
   const int nreg = a.tiles_x * a.tiles_y * ((L.n[2] + a.zc - 1) / a.zc);
-  hipLaunchKernelGGL(list_scan2_kernel, dim3(1), dim3(1024), 0, L.stream, a, nreg);
+  hipLaunchKernelGGL(list_scan2_kernel, dim3(2), dim3(1024), 0, L.stream, a, nreg);
 #define WL2_FL(S, H, W) \
   hipLaunchKernelGGL((weno_flist3d_kernel<O, S, H, W>), dim3(1024), dim3(128), 0, L.stream, a, L.g, L.ph)
   if (w0 && sp == SPLIT_LLF && hy == HYB_PER_FIELD) WL2_FL(SPLIT_LLF, HYB_PER_FIELD, W_L2IS);
