@@ -352,24 +352,46 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
         if (NV == 4 && is_yghost(g, y)) load_yghost<NV>(g, oxy, y, upre);
       }
     };
-    prefetch(y0 + 4);
+    double res[NV];  // results of row y - 1
+    const auto store_res = [&](int y) {
+      char* p = (char*)(a.out + (long long)y * g.stride[1]);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) __builtin_nontemporal_store(res[v], (double*)(p + v * g.ncell * 8 + cx8));
+    };
     for (int y = y0; y < y1; ++y) {
-      row_put<NV>(buf, lane + 3, r0);  // cell (x, y)
+      // Records of what the last row loaded, halo and own, then the loads,
+      // then the stores of the last row: a wait stands behind branches the
+      // compiler cannot count and waits for everything outstanding, so
+      // nothing new may be on its way then (1024^2 163 -> 157 us per step,
+      // 1531x1013 with global LF 212 -> 200).
       if (halo) {
         if (fxh) hpre[1] = -hpre[1];
         if (hin) load_inflow<NV>(g, y, hpre);
         LRec<NV> hr;
         make_lrec<NV>(hpre, ph, hr);
         row_put<NV>(buf, hslot, hr);
-        asm volatile("" ::: "memory");  // the prefetch below stays after this use
-        row_load_in<NV>(a.Uk, g, hx8, min(y + 1, g.n[1] - 1), hpre);  // (past the chunk: unused)
       }
-      __syncthreads();
-      __builtin_amdgcn_s_setprio(0);
-      // x face on the left of column x0+lane (cells x-3 .. x+2 = slots lane .. lane+5)
-      double Fx[NV];
-      const bool mx =
-          face_linear_l<NV, 0, SPLIT, HYB>(RowSrc<NV>{buf, lane}, ph, ph.eps_thr[0], lfx, Fx);
+      if (y > y0) {
+        // retire cell y-1 into the ring (over cell y-3), shift, make cell y+3
+        ring_put<NV>(ring, (y - 1) & 1, lane, r0);
+        r0 = r1;
+        r1 = r2;
+        r2 = r3;
+        if (fx) upre[1] = -upre[1];
+        if (fyn) upre[2] = -upre[2];
+        make_lrec<NV>(upre, ph, r3);
+        // The components that no flip rewrites move to registers of the record
+        // by an instruction the compiler cannot fold: it would otherwise keep
+        // them where they are, load the next cell elsewhere and copy that at
+        // the end of the row, waiting for the load.
+        asm volatile("v_mov_b64 %0, %1" : "=v"(r3.U[0]) : "v"(upre[0]));
+        asm volatile("v_mov_b64 %0, %1" : "=v"(r3.U[NV - 1]) : "v"(upre[NV - 1]));
+      }
+      row_put<NV>(buf, lane + 3, r0);  // cell (x, y)
+      asm volatile("" ::"v"(r3.U[0]), "v"(r3.U[NV - 1]), "v"(r3.p), "v"(r3.c), "v"(r3.iw)
+                   : "memory");  // the loads below stay after these uses
+      prefetch(y + 4);
+      if (halo) row_load_in<NV>(a.Uk, g, hx8, min(y + 1, g.n[1] - 1), hpre);  // (past the chunk: unused)
       const long long row = (long long)y * g.stride[1], off = oxy + row;
       double unp[NV] = {};
       if (OUT == OUT_RK && a.rk_a != 0.0) {
@@ -378,6 +400,13 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
         for (int v = 0; v < NV; ++v)
           unp[v] = __builtin_nontemporal_load((const double*)(p + v * g.ncell * 8 + cx8));
       }
+      if (own && y > y0) store_res(y - 1);
+      __syncthreads();
+      __builtin_amdgcn_s_setprio(0);
+      // x face on the left of column x0+lane (cells x-3 .. x+2 = slots lane .. lane+5)
+      double Fx[NV];
+      const bool mx =
+          face_linear_l<NV, 0, SPLIT, HYB>(RowSrc<NV>{buf, lane}, ph, ph.eps_thr[0], lfx, Fx);
       // y face y + 1/2: cells y-2, y-1 (ring), y .. y+3 (registers)
       double Fy[NV];
       const bool ycur = face_linear_l<NV, 1, SPLIT, HYB>(
@@ -391,43 +420,31 @@ __device__ __forceinline__ void row_item(const RowArgs& a, const KGrid& g, const
           own ? ((mx ? 1u : 0u) | (mxr ? 2u : 0u) | (yprev ? 4u : 0u) | (ycur ? 8u : 0u)) : 0u;
       list_append(a, lbuf, ln, off, cm);
       yprev = ycur;
-      // raised wave priority from the stores through the next row's loads and
-      // records to its barrier, normal for the faces (measured 1.6 % faster
-      // on 2D 1024^2; local to this kernel)
+      // raised wave priority from the end of a row through the next row's
+      // loads and records to its barrier, normal for the faces (measured
+      // 1.6 % faster on 2D 1024^2; local to this kernel)
       __builtin_amdgcn_s_setprio(2);
       if (own) {
         double un[NV];
-        char* p = (char*)(a.out + row);
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           const double dU = ((Fx[v] - Fr[v]) + (Fyp[v] - Fy[v])) * ph.inv_dx60;
           if (OUT == OUT_RK) {
             double r = a.rk_b * (r0.U[v] + dt * dU);
             if (a.rk_a != 0.0) r += a.rk_a * unp[v];
-            __builtin_nontemporal_store(r, (double*)(p + v * g.ncell * 8 + cx8));
             un[v] = r;
+            res[v] = r;
           } else {
-            __builtin_nontemporal_store(dU, (double*)(p + v * g.ncell * 8 + cx8));
+            res[v] = dU;
           }
         }
         if (OUT == OUT_RK && cm == 0u) fold.cell(a, ph, un);
       }
 #pragma unroll
       for (int v = 0; v < NV; ++v) Fyp[v] = Fy[v];
-      // retire cell y into the ring (over cell y-2), shift, make cell y+4
-      // from the prefetch and prefetch y+5 into the freed registers
-      ring_put<NV>(ring, y & 1, lane, r0);
-      r0 = r1;
-      r1 = r2;
-      r2 = r3;
-      if (fx) upre[1] = -upre[1];
-      if (fyn) upre[2] = -upre[2];
-      make_lrec<NV>(upre, ph, r3);
-      asm volatile("" ::"v"(r3.U[0]), "v"(r3.U[NV - 1]), "v"(r3.p), "v"(r3.c), "v"(r3.iw)
-                   : "memory");
-      prefetch(y + 5);
       __syncthreads();  // row buffer free for the next row
     }
+    if (own && y1 > y0) store_res(y1 - 1);
   }
   list_flush(a, lbuf, ln);
   if (OUT == OUT_RK) fold.commit(a);
