@@ -655,9 +655,15 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
   // by face lists (3 entries per cell)
   const bool hyb3 = c->dim == 3 && (p->hybrid == WL2_HYB_PER_FIELD || p->hybrid == WL2_HYB_PER_FACE);
   const bool weno3 = c->dim == 3 && p->hybrid == WL2_HYB_WENO_ONLY && nx <= WENO3D_MAX_NX;
-  if (ok && (weno3 || hyb3))
+  if (ok && (weno3 || hyb3)) {
     ok = hipMalloc(&c->fo3, sizeof(double) * (weno3 ? 10 * (size_t)c->ncell : fused3d_face_doubles(c->n))) ==
          hipSuccess;
+    if (!ok && weno3 && p->split != WL2_SPLIT_LLF) {  // too large for the sums: corrections per cell
+      (void)hipGetLastError();
+      c->fo3 = nullptr;
+      ok = true;
+    }
+  }
   if (ok && hyb3)
     ok = hipMalloc(&c->flist, sizeof(unsigned int) * fused3d_flist_entries(c->n)) == hipSuccess;
   if (ok && c->dim == 2 && p->split == WL2_SPLIT_LF)
