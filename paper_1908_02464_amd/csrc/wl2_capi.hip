@@ -162,11 +162,12 @@ bool use_row(const weno_l2is_ctx* c) { return c->dim <= 2 && c->path != WL2_PATH
 // 2D stages with the corrections in place (tile2d_kernel): every grid whose
 // faces all take the WENO flux, else grids below TILE_MAX_CELLS, where launches
 // and the chain of a stage set the time, not its work.  Measured us per step,
-// tile against row kernel and corrections (four quadrants, LLF): 64^2 31
-// against 52, 256^2 39 / 69, 512^2 71 / 109, 724^2 117 / 129, 1024^2 203 / 180;
+// tile against row kernel and corrections (four quadrants, LLF / global LF):
+// 64^2 33 against 51 / 38 against 61, 256^2 40, 65 / 44, 74, 512^2 72, 97 / 90,
+// 107, 640^2 98, 106 / 121, 116, 724^2 120, 116 / 148, 125, 1024^2 203, 155;
 // every face WENO at 1024^2 644 / 1251.  A tuned rows-per-item or per-cell
 // corrections (WL2_PATH_FUSED_CELLS) ask for the row kernel.
-constexpr long long TILE_MAX_CELLS = 5ll << 17;
+constexpr long long TILE_MAX_CELLS = 7ll << 16;
 bool use_tile(const weno_l2is_ctx* c) {
   if (c->dim != 2 || c->zchunk > 0 || (c->path != WL2_PATH_AUTO && c->path != WL2_PATH_FUSED)) return false;
   return c->p.hybrid == WL2_HYB_WENO_ONLY || c->ncell < TILE_MAX_CELLS;
