@@ -129,8 +129,10 @@ __device__ __forceinline__ void tile2d_item(const TileArgs& ta, const KGrid& g, 
     dt = a.clock != nullptr
              ? clock_dt_wave(a.clock, a.cfl_dx, a.s_floor, lead && threadIdx.x == 0)
              : a.ctl->dt;
-    if (!(dt > 0.0)) return;  // finished run: leave the state untouched (uniform)
+    // (a stopped step's clock too: the CFL maximum that it found must not meet
+    // the next reduction's)
     if (ta.commit != nullptr && lead && threadIdx.x == 0) clock_commit(ta.commit);
+    if (!(dt > 0.0)) return;  // finished run: leave the state untouched (uniform)
   }
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
