@@ -33,33 +33,39 @@ hipError_t tile2d_launch(const RowLaunch& L, int rows) {
   const int tiles_x = (L.g.n[0] + RT - 1) / RT;
   const long long blocks = (long long)tiles_x * ((L.g.n[1] + rows - 1) / rows);
   if (blocks < 1 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 gr((unsigned)blocks);
+  // a launch holds at most 2^32 - 1 lanes (9.6 M tiles): more go in several
+  // (their order does not matter: only tile 0 writes what the others read in
+  // a later stage)
+  const int most = (int)(0xffffffffLL / ((2 * rows + 1) * 64));
   const bool w0 = L.ph.weights == W_L2IS;
   // builds: the per-field switch with LLF or global LF splitting and the
   // weights of Eq.(28) fixed at compile time, any other scheme read at run time
-#define WL2_TILE(R, O)                                                                               \
-  do {                                                                                               \
-    if (w0 && L.fast == 1)                                                                           \
-      hipLaunchKernelGGL((tile2d_kernel<R, O, SPLIT_LLF, HYB_PER_FIELD, W_L2IS>), gr,                 \
-                         dim3((2 * R + 1) * 64), 0, L.stream, ta, L.g, L.ph, tiles_x);                 \
-    else if (w0 && L.fast == 2)                                                                      \
-      hipLaunchKernelGGL((tile2d_kernel<R, O, SPLIT_LF, HYB_PER_FIELD, W_L2IS>), gr,                  \
-                         dim3((2 * R + 1) * 64), 0, L.stream, ta, L.g, L.ph, tiles_x);                 \
-    else                                                                                             \
-      hipLaunchKernelGGL((tile2d_kernel<R, O, -1, -1, -1>), gr, dim3((2 * R + 1) * 64), 0, L.stream, \
-                         ta, L.g, L.ph, tiles_x);                                                     \
+#define WL2_TILE_BUILD(R, O, S, H, W) \
+  hipLaunchKernelGGL((tile2d_kernel<R, O, S, H, W>), gr, dim3((2 * R + 1) * 64), 0, L.stream, ta, L.g, L.ph, tiles_x, first)
+#define WL2_TILE(R, O)                                                              \
+  do {                                                                              \
+    if (w0 && L.fast == 1) WL2_TILE_BUILD(R, O, SPLIT_LLF, HYB_PER_FIELD, W_L2IS);     \
+    else if (w0 && L.fast == 2) WL2_TILE_BUILD(R, O, SPLIT_LF, HYB_PER_FIELD, W_L2IS); \
+    else WL2_TILE_BUILD(R, O, -1, -1, -1);                                          \
   } while (0)
 #define WL2_TILE_OUT(R)                                \
   do {                                                 \
     if (L.out_kind == OUT_RK) WL2_TILE(R, OUT_RK);     \
     else WL2_TILE(R, OUT_WRITE);                       \
   } while (0)
-  if (rows == 1) WL2_TILE_OUT(1);
-  else if (rows == 3) WL2_TILE_OUT(3);
-  else return hipErrorInvalidValue;
+  if (rows != 1 && rows != 3) return hipErrorInvalidValue;
+  hipError_t e = hipSuccess;
+  for (long long f = 0; f < blocks && e == hipSuccess; f += most) {
+    const int first = (int)f;
+    const dim3 gr((unsigned)(blocks - f < most ? blocks - f : most));
+    if (rows == 1) WL2_TILE_OUT(1);
+    else WL2_TILE_OUT(3);
+    e = hipGetLastError();
+  }
+  return e;
 #undef WL2_TILE_OUT
 #undef WL2_TILE
-  return hipGetLastError();
+#undef WL2_TILE_BUILD
 }
 
 }  // namespace wl2

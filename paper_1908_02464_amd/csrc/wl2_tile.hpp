@@ -215,12 +215,13 @@ __device__ __forceinline__ void tile2d_item(const TileArgs& ta, const KGrid& g, 
   }
 }
 
+// Tiles first + blockIdx.x.
 template <int R, int OUT, int SPLIT, int HYB, int W>
 __global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta, KGrid g, KPhys ph,
-                                                                    int tiles_x) {
+                                                                    int tiles_x, int first) {
   __shared__ TileShared<R> sh;
-  tile2d_item<R, OUT, SPLIT, HYB, W>(ta, g, ph, (blockIdx.x % tiles_x) * RT, (blockIdx.x / tiles_x) * R,
-                                     blockIdx.x == 0, sh);
+  const int b = first + (int)blockIdx.x;
+  tile2d_item<R, OUT, SPLIT, HYB, W>(ta, g, ph, (b % tiles_x) * RT, (b / tiles_x) * R, b == 0, sh);
 }
 
 }  // namespace wl2

@@ -1,0 +1,44 @@
+"""Which kernels a call launches, over which grid, for shapes that no test
+device holds, and what a context keeps when memory is short: the library's host
+side over a stand-in for the HIP runtime (hip_stub.c), without a GPU."""
+from __future__ import annotations
+
+import pytest
+
+from hip_stub import host_calls  # noqa: F401  (fixture)
+
+
+def test_ordinary_calls_launch(host_calls):
+    """The stand-in serves the library: a step of each dimension launches its
+    kernels within the runtime's limits, and destroy frees what create took."""
+    out = host_calls(r'''
+out = []
+for shape in ((200, 1, 1), (300, 200, 1), (800, 700, 1), (20, 18, 17)):
+    h = create(shape)
+    stub.stub_clear()
+    rc = L.weno_l2is_step(h, U, 1e-3)
+    out.append([rc, launches()])
+    L.weno_l2is_destroy(h)
+    out[-1].append(stub.stub_used())
+''')
+    for (rc, ls, used), k in zip(out, ("row_kernel<3", "tile2d_kernel", "row_kernel<4", "fused3d_kernel")):
+        assert rc == 0 and used == 0
+        assert sum(k in r[0] for r in ls) == 3
+
+
+@pytest.mark.parametrize("nx,ny,kw", [(2, 40_000_000, {"hybrid": 2}), (64, 21_000_001, {"hybrid": 2, "split": 1}),
+                                      (1, 100_000_000, {"hybrid": 2, "split": 2})])
+def test_tall_grids_launch(host_calls, nx, ny, kw):
+    """2D grids with every face WENO of more tiles than one launch holds:
+    accepted, and every tile has its workgroup."""
+    rcs, ls = host_calls(f'''
+h = create(({nx}, {ny}, 1), **{kw!r})
+stub.stub_clear()
+rcs = [L.weno_l2is_rhs_ctx(h, U, V), L.weno_l2is_step(h, U, 1e-9), L.weno_l2is_advance(h, U, 2, 1.0)]
+out = [rcs, launches()]
+''')
+    assert rcs == [0, 0, 0]
+    tiles = -(-nx // 63) * -(-ny // 3)
+    stages = [r for r in ls if "tile2d_kernel<3" in r[0]]
+    assert all(r[1] * r[4] < 1 << 32 and r[2:4] == [1, 1] and r[4] == 448 for r in stages)
+    assert sum(r[1] for r in stages) == (1 + 3 + 6) * tiles

@@ -1,0 +1,43 @@
+"""Grids at the ends of the accepted shapes, on the device."""
+from __future__ import annotations
+
+import pytest
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+G = 1.4
+
+
+def _flow(nx, ny):
+    """A 2D state made on the device: jumps and noise over the whole grid."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(nx + ny)
+    U = torch.empty((4, 1, ny, nx), dtype=torch.float64, device="cuda")
+    n = nx * ny
+    rho = 1.0 + 0.5 * ((torch.arange(n, device="cuda") // 7) % 3).double() + 0.1 * torch.rand(n, generator=g, device="cuda", dtype=torch.float64)
+    U[0] = rho.view(1, ny, nx)
+    for k in (1, 2):
+        U[k] = (rho * (0.2 * torch.rand(n, generator=g, device="cuda", dtype=torch.float64) - 0.1)).view(1, ny, nx)
+    U[3] = (2.5 * rho + 0.5 * (U[1] ** 2 + U[2] ** 2).view(-1) / rho).view(1, ny, nx)
+    return U
+
+
+def test_more_tiles_than_a_launch_holds():
+    """A narrow grid of 10 M tiles (two launches per stage): the bits of the
+    row kernel and its corrections."""
+    import torch
+    from paper_1908_02464_amd import capi
+    nx, ny = 2, 30_000_001
+    say(f"[extents] {nx}x{ny}")
+    U = _flow(nx, ny)
+    p = capi.params_default(nx, ny, 1, 1.0, bc=[0, 0, 1, 2, 1, 1], hybrid=2)
+    ctx = capi.Context(nx, ny, 1, 1.0, G, p)
+    D = [torch.full_like(U, float("nan")) for _ in range(2)]
+    for rows, d in zip((0, 20), D):
+        ctx.tune(zchunk=rows)
+        ctx.rhs(U, d)
+        torch.cuda.synchronize()
+    ctx.close()
+    assert bool(torch.isfinite(D[0]).all()) and float(D[0].abs().max()) > 0.1
+    assert torch.equal(D[0], D[1])
