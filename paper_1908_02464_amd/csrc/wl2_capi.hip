@@ -166,10 +166,13 @@ bool use_row(const weno_l2is_ctx* c) { return c->dim <= 2 && c->path != WL2_PATH
 // 64^2 33 against 51 / 38 against 61, 256^2 40, 65 / 44, 74, 512^2 72, 97 / 90,
 // 107, 640^2 98, 106 / 121, 116, 724^2 120, 116 / 148, 125, 1024^2 203, 155;
 // every face WENO at 1024^2 644 / 1251.  A tuned rows-per-item or per-cell
-// corrections (WL2_PATH_FUSED_CELLS) ask for the row kernel.
+// corrections (WL2_PATH_FUSED_CELLS) ask for the row kernel, whose column offsets
+// have 32 bits: a wider grid takes the tile kernel all the same (the same bits).
 constexpr long long TILE_MAX_CELLS = 7ll << 16;
 bool use_tile(const weno_l2is_ctx* c) {
-  if (c->dim != 2 || c->zchunk > 0 || (c->path != WL2_PATH_AUTO && c->path != WL2_PATH_FUSED)) return false;
+  if (c->dim != 2 || c->path == WL2_PATH_SWEEPS) return false;
+  if (c->n[0] > ROW_MAX_NX) return true;
+  if (c->zchunk > 0 || c->path == WL2_PATH_FUSED_CELLS) return false;
   return c->p.hybrid == WL2_HYB_WENO_ONLY || c->ncell < TILE_MAX_CELLS;
 }
 

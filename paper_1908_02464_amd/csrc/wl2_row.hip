@@ -95,6 +95,7 @@ hipError_t row_launch(const RowLaunch& L) {
                   L.rk_b, L.list, L.list_n, nullptr,
                   L.out_kind == OUT_RK ? L.cfl : nullptr, L.out_kind == OUT_RK ? L.clock : nullptr,
                   L.cfl_dx, L.s_floor, L.lf_in, L.lf_out, L.lf_clear};
+  if (L.nvar == 4 && L.g.n[0] > ROW_MAX_NX) return hipErrorInvalidValue;
   const int tiles_x = (L.g.n[0] + RT - 1) / RT;
   const int ych = L.nvar == 3 ? 1 : (L.ych < 1 ? 1 : (L.ych > ROW_MAX_YCH ? ROW_MAX_YCH : L.ych));
   const long long chunks = L.nvar == 3 ? 1 : (L.g.n[1] + ych - 1) / ych;

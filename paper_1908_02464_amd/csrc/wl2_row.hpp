@@ -169,8 +169,8 @@ struct Win6Src {  // six records in registers
 };
 
 // Row iy (in the grid) of the column at x: the row's address is uniform in the
-// wavefront and the column a 32-bit byte offset (nx <= 2^29: a larger grid's
-// arrays do not fit the device).
+// wavefront and the column a 32-bit byte offset (nx <= ROW_MAX_NX: wider grids,
+// of which those of two and three rows fit the device, take the tile kernel).
 template <int NV>
 __device__ __forceinline__ void row_load_in(const double* __restrict__ U, const KGrid& g, unsigned x8, int iy,
                                             double (&u)[NV]) {

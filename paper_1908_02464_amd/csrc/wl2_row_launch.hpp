@@ -8,6 +8,7 @@ namespace wl2 {
 
 constexpr int ROW_TILE = 63;     // columns per work item (one wavefront)
 constexpr int ROW_MAX_YCH = 62;  // rows per work item (flag bits per row)
+constexpr int ROW_MAX_NX = 1 << 29;  // columns of a 2D grid: a 32-bit byte offset
 
 struct YGhostRule;
 
@@ -48,7 +49,8 @@ struct RowLaunch {
 };
 
 // The launches of one stage, in stream order: the row kernel and the
-// nonlinear corrections of the listed cells.  The list counter of a stage is
+// nonlinear corrections of the listed cells (2D grids up to ROW_MAX_NX wide).
+// The list counter of a stage is
 // cleared by the previous stage's correction kernel; row_reset clears both
 // counters (before the first stage, or after a failed launch).
 hipError_t row_reset(const RowLaunch& L);

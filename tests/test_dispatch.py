@@ -42,3 +42,26 @@ out = [rcs, launches()]
     stages = [r for r in ls if "tile2d_kernel<3" in r[0]]
     assert all(r[1] * r[4] < 1 << 32 and r[2:4] == [1, 1] and r[4] == 448 for r in stages)
     assert sum(r[1] for r in stages) == (1 + 3 + 6) * tiles
+
+
+@pytest.mark.parametrize("kw", [{}, {"split": 1}, {"bc": [1, 1, 4, 5, 1, 1]}])
+def test_wide_grids_take_the_tile_kernel(host_calls, kw):
+    """2D grids wider than the row kernel's 32-bit column offsets reach run on
+    the tile kernel, however they are tuned; the widest that they reach, on the
+    row kernel."""
+    out = host_calls(f'''
+out = []
+for nx in (1 << 29, (1 << 29) + 1, 700_000_000):
+    h = create((nx, 2, 1), **{kw!r})
+    for tune in ((0, 0, 0), (2, 0, 0), (0, 2, 0), (3, 0, 0)):
+        assert L.weno_l2is_tune(h, *tune) == 0
+        stub.stub_clear()
+        rcs = [L.weno_l2is_rhs_ctx(h, U, V), L.weno_l2is_step(h, U, 1e-9), L.weno_l2is_advance(h, U, 2, 1.0)]
+        out.append([nx, rcs, launches()])
+''')
+    for nx, rcs, ls in out:
+        assert rcs == [0, 0, 0]
+        row = sum("row_kernel<4" in r[0] for r in ls)
+        tiles = sum(r[1] for r in ls if "tile2d_kernel<3" in r[0])
+        assert (row, tiles) == ((10, 0) if nx == 1 << 29 else (0, 10 * -(-nx // 63)))
+        assert nx == 1 << 29 or not any("ghost_fill" in r[0] for r in ls)  # the tile kernel forms them

@@ -41,3 +41,41 @@ def test_more_tiles_than_a_launch_holds():
     ctx.close()
     assert bool(torch.isfinite(D[0]).all()) and float(D[0].abs().max()) > 0.1
     assert torch.equal(D[0], D[1])
+
+
+def test_columns_past_32_bit_offsets():
+    """A 2D grid wider than 2^29 columns (2^32 bytes a row): dU/dt around the
+    columns where a 32-bit byte offset would wrap, and at both ends, carries
+    the bits of small grids cut out there."""
+    import torch
+    from paper_1908_02464_amd import capi
+    nx, ny = (1 << 29) + 500, 2
+    need = nx * ny * 8 * 4 * 2 + nx * ny * (3 * 32 + 8 + 68)  # U, dU/dt and the context
+    free, _ = torch.cuda.mem_get_info()
+    if free < need + (8 << 30):
+        pytest.skip(f"{free >> 30} GiB of device memory free, {need >> 30} needed")
+    say(f"[extents] {nx}x{ny}: {need >> 30} GiB")
+    U = torch.empty((4, 1, ny, nx), dtype=torch.float64, device="cuda")
+    step = 1 << 26
+    for x in range(0, nx, step):
+        n = min(step, nx - x)
+        U[:, :, :, x:x + n] = _flow(n, ny)
+    torch.cuda.empty_cache()
+    D = torch.full_like(U, float("nan"))
+    p = capi.params_default(nx, ny, 1, 1.0, bc=[1, 1, 0, 0, 1, 1])
+    ctx = capi.Context(nx, ny, 1, 1.0, G, p)
+    ctx.rhs(U, D)
+    torch.cuda.synchronize()
+    ctx.close()
+    w = 200
+    for x in (0, (1 << 28) - 100, (1 << 29) - 100, nx - w):
+        V = U[:, :, :, x:x + w].contiguous()
+        q = capi.params_default(w, ny, 1, 1.0, bc=[1, 1, 0, 0, 1, 1], thr_L=(p.thr_L[0], p.thr_L[1], 1.0))
+        E = torch.empty_like(V)
+        c = capi.Context(w, ny, 1, 1.0, G, q)
+        c.rhs(V, E)
+        torch.cuda.synchronize()
+        c.close()
+        a, b = 0 if x == 0 else 3, w if x == nx - w else w - 3  # cells whose stencils lie in the cut
+        assert float(E.abs().max()) > 0.01
+        assert torch.equal(D[:, :, :, x + a:x + b], E[:, :, :, a:b]), x
