@@ -123,7 +123,9 @@ hipError_t wait_upload(weno_l2is_batch* b) {
   return hipEventSynchronize(b->ev_upload);
 }
 
+// The graph's launches may still be running: its kernel arguments live with it.
 void drop_graph(weno_l2is_batch* b) {
+  if (b->gexec) (void)hipStreamSynchronize(b->stream);
   if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
   b->gexec = nullptr;

@@ -65,3 +65,51 @@ for nx in (1 << 29, (1 << 29) + 1, 700_000_000):
         tiles = sum(r[1] for r in ls if "tile2d_kernel<3" in r[0])
         assert (row, tiles) == ((10, 0) if nx == 1 << 29 else (0, 10 * -(-nx // 63)))
         assert nx == 1 << 29 or not any("ghost_fill" in r[0] for r in ls)  # the tile kernel forms them
+
+
+# a batched engine; admit(k): a run of scheme k (0: the default one, whose stage
+# kernels are a build of their own) from device memory
+BATCH = r'''
+b = C.c_void_p()
+assert L.weno_l2is_batch_create(1 << 28, 64, None, C.byref(b)) == 0
+def admit(scheme, shape=(100, 80, 1)):
+    p = capi.params_default(*shape, 0.1, split=2 if scheme else 0)
+    slot = C.c_int(-1)
+    assert L.weno_l2is_batch_admit(b, *shape, 0.1, 1.4, C.byref(p), U, 0, 1.0, C.byref(slot), None) == 0
+    return slot.value
+def fetch(slot):
+    assert L.weno_l2is_batch_fetch(b, slot, V, 0, None, None, None) == 0
+'''
+
+
+def test_batch_graph_outlives_its_launches(host_calls):
+    """No captured graph is destroyed before the stream has run what was
+    launched of it: a run of another scheme class, a new launch shape, more
+    work items than the tables held, and destroy."""
+    lines = host_calls(BATCH + r'''
+admit(0); admit(0)
+assert L.weno_l2is_batch_advance(b, 3) == 0
+s = admit(1)
+assert L.weno_l2is_batch_advance(b, 2) == 0
+assert L.weno_l2is_batch_tune(b, 1, 0) == 0
+assert L.weno_l2is_batch_advance(b, 2) == 0
+assert L.weno_l2is_batch_tune(b, 0, 512) == 0
+assert L.weno_l2is_batch_advance(b, 2) == 0
+admit(0, (400, 400, 1)); admit(0, (700, 700, 1))
+assert L.weno_l2is_batch_advance(b, 2) == 0
+fetch(s)
+assert L.weno_l2is_batch_advance(b, 2) == 0
+L.weno_l2is_batch_destroy(b)
+out = log()
+''')
+    running, destroyed = set(), 0
+    for l in lines:
+        op, *a = l.split()
+        if op == "graph":
+            running.add(a[0])
+        elif op == "sync":
+            running.clear()
+        elif op == "destroy":
+            assert a[0] not in running, lines
+            destroyed += 1
+    assert destroyed >= 3 and sum(l.startswith("graph") for l in lines) == 13
