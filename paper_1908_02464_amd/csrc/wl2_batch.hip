@@ -4,7 +4,8 @@
 // sequence captured once in a hipGraph (the kernels read the tables from
 // device memory, so the graph stays valid while runs come and go; it is
 // captured again only when a table outgrows its buffer or the launch shape
-// changes).
+// changes; one graph per build of the stage kernels, so that runs of other
+// schemes come and go without a capture).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -77,9 +78,11 @@ struct weno_l2is_batch {
   hipEvent_t ev_state = nullptr, ev_upload = nullptr;
   bool state_pending = false, upload_pending = false;
   bool dirty = true;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  bool graph_fast = true;  // the captured graph's stage kernels: the default scheme only
+  // the step's graph with each build of the stage kernels: [1] while every
+  // admitted run has the default scheme, [0] else
+  hipGraph_t graph[2] = {nullptr, nullptr};
+  hipGraphExec_t gexec[2] = {nullptr, nullptr};
+  int fast = 1;  // the graph that serves the admitted runs
   int rows = ROWS_DEFAULT;
   int row_blocks = ROW_BLOCKS_DEFAULT;
 };
@@ -123,17 +126,19 @@ hipError_t wait_upload(weno_l2is_batch* b) {
   return hipEventSynchronize(b->ev_upload);
 }
 
-// The graph's launches may still be running: its kernel arguments live with it.
-void drop_graph(weno_l2is_batch* b) {
-  if (b->gexec) (void)hipStreamSynchronize(b->stream);
-  if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
-  b->gexec = nullptr;
-  b->graph = nullptr;
+// The graphs' launches may still be running: their kernel arguments live with them.
+void drop_graphs(weno_l2is_batch* b) {
+  if (b->gexec[0] || b->gexec[1]) (void)hipStreamSynchronize(b->stream);
+  for (int k = 0; k < 2; ++k) {
+    if (b->gexec[k]) (void)hipGraphExecDestroy(b->gexec[k]);
+    if (b->graph[k]) (void)hipGraphDestroy(b->graph[k]);
+    b->gexec[k] = nullptr;
+    b->graph[k] = nullptr;
+  }
 }
 
 // Item buffers of dimension index d (0: 1D, 1: 2D) for at least n items; a
-// new buffer invalidates the captured graph (its kernels hold the pointer).
+// new buffer invalidates the captured graphs (their kernels hold the pointer).
 hipError_t reserve_items(weno_l2is_batch* b, int d, long long n) {
   if (n <= b->item_cap[d]) return hipSuccess;
   if (n > 0x3fffffffLL) return hipErrorInvalidValue;
@@ -153,7 +158,7 @@ hipError_t reserve_items(weno_l2is_batch* b, int d, long long n) {
   b->d_items[d] = dn;
   b->h_items[d] = hn;
   b->item_cap[d] = (int)cap;
-  drop_graph(b);
+  drop_graphs(b);
   return hipSuccess;
 }
 
@@ -193,10 +198,7 @@ hipError_t upload_tables(weno_l2is_batch* b) {
       ++nch;
     }
   }
-  if (fast != b->graph_fast) {
-    b->graph_fast = fast;
-    drop_graph(b);  // the other build of the stage kernels
-  }
+  b->fast = fast ? 1 : 0;
   b->h_counts[0] = nch;
   b->h_counts[1] = nact;
   b->h_counts[2] = ni[0];
@@ -237,9 +239,9 @@ hipError_t enqueue_step(weno_l2is_batch* b) {
     WL2_BATCH_STAGE(R, 2, F);  \
   } while (0)
   const bool one = tile_rows(b->rows) == 1;
-  if (one && b->graph_fast) WL2_BATCH_STAGES(1, true);
+  if (one && b->fast) WL2_BATCH_STAGES(1, true);
   else if (one) WL2_BATCH_STAGES(1, false);
-  else if (b->graph_fast) WL2_BATCH_STAGES(3, true);
+  else if (b->fast) WL2_BATCH_STAGES(3, true);
   else WL2_BATCH_STAGES(3, false);
 #undef WL2_BATCH_STAGE
 #undef WL2_BATCH_STAGES
@@ -247,7 +249,8 @@ hipError_t enqueue_step(weno_l2is_batch* b) {
 }
 
 hipError_t ensure_graph(weno_l2is_batch* b) {
-  if (b->gexec) return hipSuccess;
+  const int k = b->fast;
+  if (b->gexec[k]) return hipSuccess;
   for (int d = 0; d < 2; ++d) {  // buffers exist before the capture
     hipError_t e = reserve_items(b, d, 1);
     if (e != hipSuccess) return e;
@@ -255,10 +258,10 @@ hipError_t ensure_graph(weno_l2is_batch* b) {
   hipError_t e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return e;
   hipError_t e2 = enqueue_step(b);
-  e = hipStreamEndCapture(b->stream, &b->graph);
+  e = hipStreamEndCapture(b->stream, &b->graph[k]);
   if (e2 != hipSuccess) return e2;
   if (e != hipSuccess) return e;
-  return hipGraphInstantiate(&b->gexec, b->graph, nullptr, nullptr, 0);
+  return hipGraphInstantiate(&b->gexec[k], b->graph[k], nullptr, nullptr, 0);
 }
 
 int herr(hipError_t e) { return e == hipSuccess ? WL2_OK : WL2_E_HIP; }
@@ -409,7 +412,7 @@ int weno_l2is_batch_advance(weno_l2is_batch* b, int n_steps) {
   if (b->active == 0) return WL2_OK;
   if ((e = ensure_graph(b)) != hipSuccess) return herr(e);
   for (int k = 0; k < n_steps; ++k)
-    if ((e = hipGraphLaunch(b->gexec, b->stream)) != hipSuccess) return herr(e);
+    if ((e = hipGraphLaunch(b->gexec[b->fast], b->stream)) != hipSuccess) return herr(e);
   hipLaunchKernelGGL(batch_gather_kernel, dim3(4), dim3(256), 0, b->stream, b->d_ctl,
                      b->d_slotlist, b->d_counts + 1, b->d_state);
   if ((e = hipGetLastError()) != hipSuccess) return herr(e);
@@ -476,11 +479,11 @@ int weno_l2is_batch_tune(weno_l2is_batch* b, int rows, int blocks) {
   if (rows && rows != b->rows) {
     b->rows = rows;
     b->dirty = true;  // the 2D items follow the rows per item
-    drop_graph(b);    // and so does the build of the stage kernels
+    drop_graphs(b);   // and so does the build of the stage kernels
   }
   if (blocks && blocks != b->row_blocks) {
     b->row_blocks = blocks;
-    drop_graph(b);  // the grid size is part of the captured launches
+    drop_graphs(b);  // the grid size is part of the captured launches
   }
   return WL2_OK;
 }
@@ -495,8 +498,7 @@ int weno_l2is_batch_usage(weno_l2is_batch* b, size_t* used_bytes, int* active) {
 void weno_l2is_batch_destroy(weno_l2is_batch* b) {
   if (!b) return;
   if (b->stream || b->pool) (void)hipStreamSynchronize(b->stream);
-  if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
+  drop_graphs(b);
   if (b->ev_state) (void)hipEventDestroy(b->ev_state);
   if (b->ev_upload) (void)hipEventDestroy(b->ev_upload);
   (void)hipFree(b->pool);

@@ -113,3 +113,21 @@ out = log()
             assert a[0] not in running, lines
             destroyed += 1
     assert destroyed >= 3 and sum(l.startswith("graph") for l in lines) == 13
+
+
+def test_batch_scheme_classes_keep_their_graphs(host_calls):
+    """Runs of another scheme that come and go switch between two captured
+    graphs; neither is captured again."""
+    lines = host_calls(BATCH + r'''
+admit(0)
+for k in range(6):
+    s = admit(1)
+    assert L.weno_l2is_batch_advance(b, 1) == 0
+    fetch(s)
+    assert L.weno_l2is_batch_advance(b, 1) == 0
+out = log()
+L.weno_l2is_batch_destroy(b)
+''')
+    graphs = [l.split()[1] for l in lines if l.startswith("graph")]
+    assert graphs == ["1", "2"] * 6
+    assert sum(l == "capture" for l in lines) == 2
