@@ -101,19 +101,23 @@ __global__ __launch_bounds__((2 * R + 1) * 64, 4) void batch_stage_kernel(
     } else {
       const BatchItem it = items2[q - n1g];
       const BGrid& G = grids[it.slot];
-      const KGrid g = G.g;
-      const KPhys ph = G.ph;
-      __builtin_assume(g.bc_lo[0] != BC_INFLOW);  // (not admitted)
-      TileArgs ta{};
-      ta.r.Uk = pool + (STAGE == 0 ? G.U : (STAGE == 1 ? G.U1 : G.U2));
-      ta.r.out = pool + (STAGE == 0 ? G.U1 : (STAGE == 1 ? G.U2 : G.U));
-      ta.r.Un = pool + G.U;
-      ta.r.ctl = ctls + it.slot;
-      ta.r.rk_a = STAGE == 0 ? 0.0 : (STAGE == 1 ? 0.75 : 1.0 / 3.0);
-      ta.r.rk_b = STAGE == 0 ? 1.0 : (STAGE == 1 ? 0.25 : 2.0 / 3.0);
-      TileShared<R>& sh = *reinterpret_cast<TileShared<R>*>(raw);
-      tile2d_item<R, OUT_RK, FAST ? SPLIT_LLF : -1, FAST ? HYB_PER_FIELD : -1, FAST ? W_L2IS : -1>(
-          ta, g, ph, it.x0, it.y0, false, sh);
+      // a finished run that waits to be fetched loads nothing (asked for beside
+      // its descriptor: all 40 runs of a mix finished, 73 -> 29 us per step)
+      if (ctls[it.slot].dt > 0.0) {
+        const KGrid g = G.g;
+        const KPhys ph = G.ph;
+        __builtin_assume(g.bc_lo[0] != BC_INFLOW);  // (not admitted)
+        TileArgs ta{};
+        ta.r.Uk = pool + (STAGE == 0 ? G.U : (STAGE == 1 ? G.U1 : G.U2));
+        ta.r.out = pool + (STAGE == 0 ? G.U1 : (STAGE == 1 ? G.U2 : G.U));
+        ta.r.Un = pool + G.U;
+        ta.r.ctl = ctls + it.slot;
+        ta.r.rk_a = STAGE == 0 ? 0.0 : (STAGE == 1 ? 0.75 : 1.0 / 3.0);
+        ta.r.rk_b = STAGE == 0 ? 1.0 : (STAGE == 1 ? 0.25 : 2.0 / 3.0);
+        TileShared<R>& sh = *reinterpret_cast<TileShared<R>*>(raw);
+        tile2d_item<R, OUT_RK, FAST ? SPLIT_LLF : -1, FAST ? HYB_PER_FIELD : -1, FAST ? W_L2IS : -1>(
+            ta, g, ph, it.x0, it.y0, false, sh);
+      }
     }
     __syncthreads();  // the LDS is free for the next item
   }
