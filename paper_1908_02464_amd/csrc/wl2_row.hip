@@ -70,22 +70,31 @@ hipError_t row_fix(const RowLaunch& L) {
 #undef WL2_FO
     return hipGetLastError();
   }
-#define WL2_FIX(NV, O)                                                                     \
-  do {                                                                                     \
-    if (L.fast == 1)                                                                       \
-      hipLaunchKernelGGL((row_fix_kernel<NV, O, SPLIT_LLF, HYB_PER_FIELD>), fgc, fb, 0, L.stream, a, L.g, L.ph); \
-    else if (L.fast == 2)                                                                  \
-      hipLaunchKernelGGL((row_fix_kernel<NV, O, SPLIT_LF, HYB_PER_FIELD>), fgc, fb, 0, L.stream, a, L.g, L.ph); \
-    else                                                                                   \
-      hipLaunchKernelGGL((row_fix_kernel<NV, O, -1, -1>), fgc, fb, 0, L.stream, a, L.g, L.ph); \
+#define WL2_FIX_BUILD(NV, O, S, H, WPE) \
+  hipLaunchKernelGGL((row_fix_kernel<NV, O, S, H, WPE>), fgc, fb, 0, L.stream, a, L.g, L.ph)
+#define WL2_FIX(NV, O, WPE)                                              \
+  do {                                                                   \
+    if (L.fast == 1) WL2_FIX_BUILD(NV, O, SPLIT_LLF, HYB_PER_FIELD, 2);      \
+    else if (L.fast == 2) WL2_FIX_BUILD(NV, O, SPLIT_LF, HYB_PER_FIELD, 2);  \
+    else WL2_FIX_BUILD(NV, O, -1, -1, WPE);                              \
   } while (0)
   if (L.nvar == 3) {
-    if (L.out_kind == OUT_RK) WL2_FIX(3, OUT_RK); else WL2_FIX(3, OUT_WRITE);
+    // two wavefronts per SIMD hold 131072 cells
+    const bool three = L.g.ncell > 131072;
+    if (L.out_kind == OUT_RK) {
+      if (three) WL2_FIX(3, OUT_RK, 3);
+      else WL2_FIX(3, OUT_RK, 2);
+    } else {
+      if (three) WL2_FIX(3, OUT_WRITE, 3);
+      else WL2_FIX(3, OUT_WRITE, 2);
+    }
   } else if (L.nvar == 4) {
-    if (L.out_kind == OUT_RK) WL2_FIX(4, OUT_RK); else WL2_FIX(4, OUT_WRITE);
+    if (L.out_kind == OUT_RK) WL2_FIX(4, OUT_RK, 2);
+    else WL2_FIX(4, OUT_WRITE, 2);
   } else {
     return hipErrorInvalidValue;
   }
+#undef WL2_FIX_BUILD
 #undef WL2_FIX
   return hipGetLastError();
 }

@@ -554,9 +554,13 @@ __device__ __forceinline__ void row_fix_fields(const RowArgs& a, const KGrid& g,
 // Single grid.  A list short enough for every cell to be in flight at once
 // (launched with 2048 workgroups: 16384 cells in 2D, 32768 in 1D) takes the
 // field-parallel mode (latency), a longer one a lane per cell (throughput).
-// 128 threads per workgroup.
-template <int NV, int OUT, int SPLIT, int HYB>
-__global__ __launch_bounds__(128) void row_fix_kernel(RowArgs a, KGrid g, KPhys ph) {
+// 128 threads per workgroup.  WPE: wavefronts per SIMD that the registers are
+// cut to.  Two hold what a lane keeps (188 to 251 VGPRs); three spill 12 to 40
+// bytes of it in 1D, and pay where a lane per cell gives more wavefronts than
+// two per SIMD hold: every face WENO, us per right-hand side, two / three,
+// 100000 cells 38 / 42, 262000 80 / 79, 400000 122 / 119, 1000000 288 / 282.
+template <int NV, int OUT, int SPLIT, int HYB, int WPE>
+__global__ __launch_bounds__(128, WPE) void row_fix_kernel(RowArgs a, KGrid g, KPhys ph) {
   // the next stage's list starts empty (no kernel of this stage uses it)
   if (a.list_clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.list_clear = 0u;
   if (a.clock != nullptr && blockIdx.x == 0 && threadIdx.x == 0) clock_commit(a.clock);
