@@ -455,8 +455,11 @@ hipError_t launch_fused(const weno_l2is_ctx* c, int out_kind, const double* Uk, 
   L.out_kind = out_kind;
   L.zc = fused_zchunk(c);
   L.wpe = c->wpe;  // the scheme's build is chosen from L.ph
-  L.fo3 = c->path == WL2_PATH_FUSED_CELLS ? nullptr : c->fo3;
-  L.flist = c->path == WL2_PATH_FUSED_CELLS ? nullptr : c->flist;
+  // (a cached right-hand-side context may hold the buffers of another switch)
+  const bool every = c->p.hybrid == WL2_HYB_WENO_ONLY;
+  const bool cells = c->path == WL2_PATH_FUSED_CELLS || (every && c->n[0] > WENO3D_MAX_NX);
+  L.fo3 = cells ? nullptr : c->fo3;
+  L.flist = cells ? nullptr : c->flist;
   const size_t ce = fused3d_count_entries(c->n);
   L.counts = c->counts;
   L.offs = c->counts ? c->counts + ce : nullptr;
@@ -469,7 +472,7 @@ hipError_t launch_fused(const weno_l2is_ctx* c, int out_kind, const double* Uk, 
   L.march = c->zchunk;
   hipError_t e = turn.reset ? fused3d_reset(L) : hipSuccess;
   if (e != hipSuccess) return turn.done(e);
-  if (L.fo3 != nullptr && c->p.hybrid == WL2_HYB_WENO_ONLY) {
+  if (L.fo3 != nullptr && every) {
     TimedLaunch tl(c, out_kind == OUT_RK ? "weno3d_rk" : "weno3d_rhs");
     return turn.done(weno3d_stage(L));
   }

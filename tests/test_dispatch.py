@@ -131,3 +131,32 @@ L.weno_l2is_batch_destroy(b)
     graphs = [l.split()[1] for l in lines if l.startswith("graph")]
     assert graphs == ["1", "2"] * 6
     assert sum(l == "capture" for l in lines) == 2
+
+
+@pytest.mark.parametrize("nx", [1 << 27, (1 << 27) + 1])
+def test_cached_rhs_keeps_to_the_3d_march_width(host_calls, nx):
+    """The stateless right-hand side of one shape with the hybrid switch (whose
+    cached context holds a face buffer), then with every face WENO: rows wider
+    than the 32-bit offsets of the kernels per direction take the stage kernel
+    with per-cell corrections, as on a context made for that scheme."""
+    out = host_calls(f'''
+def names():
+    return sorted(n.split("(")[0].split("<")[0].split("::")[-1] for n, *_ in launches())
+out = []
+shape = ({nx}, 2, 2)
+for hybrid in (0, 2, 0):
+    p = capi.params_default(*shape, 0.1, hybrid=hybrid)
+    stub.stub_clear()
+    assert L.weno_l2is_rhs(U, *shape, 0.1, 1.4, C.byref(p), V) == 0
+    out.append(names())
+h = create(shape, hybrid=2)
+stub.stub_clear()
+assert L.weno_l2is_rhs_ctx(h, U, V) == 0
+out.append(names())
+''')
+    hybrid, every, again, ctx = out
+    march = nx <= 1 << 27
+    assert ("weno3d_x_kernel" in every) == march and ("weno_fix3d_kernel" in every) == (not march)
+    assert "weno_flist3d_kernel" not in every
+    assert [n for n in ctx if "reset" not in n] == [n for n in every if "reset" not in n]
+    assert "weno_flist3d_kernel" in hybrid and "weno_flist3d_kernel" in again
