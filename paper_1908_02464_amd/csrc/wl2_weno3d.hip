@@ -7,6 +7,16 @@ namespace wl2 {
 
 namespace {
 
+// Cells that a lane marches through: the tuned value, else the balanced one; at
+// least as many as keep a launch of `groups` wavefronts per chunk within the
+// runtime's 2^32 - 1 lanes.
+int march(const FusedLaunch& L, long long groups, int n) {
+  const int len = L.march > 0 ? L.march : balanced_chunk(groups, n, 1, 64);
+  const long long chunks = (0xffffffffLL / 64) / groups;
+  const long long least = chunks > 0 ? (n + chunks - 1) / chunks : n;
+  return len > least ? len : (int)least;
+}
+
 template <int OUT, int SPLIT, int W>
 hipError_t launch(const FusedLaunch& L) {
   const Weno3dArgs a{L.Uk,   L.out,        L.Un, L.ctl, L.rk_a,
@@ -14,8 +24,7 @@ hipError_t launch(const FusedLaunch& L) {
   const long long nx = L.n[0], ny = L.n[1], nz = L.n[2];
   const long long bx = ((nx + 1) * ny * nz + WX_FACES - 1) / WX_FACES;
   const long long gy = (nx * nz + 63) / 64, gz = (nx * ny + 63) / 64;
-  const int ly = L.march > 0 ? L.march : balanced_chunk(gy, L.n[1], 1, 64);
-  const int lz = L.march > 0 ? L.march : balanced_chunk(gz, L.n[2], 1, 64);
+  const int ly = march(L, gy, L.n[1]), lz = march(L, gz, L.n[2]);
   const long long by = gy * ((ny + ly - 1) / ly), bz = gz * ((nz + lz - 1) / lz);
   if (bx > 0x7fffffffLL || by > 0x7fffffffLL || bz > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 b(64);

@@ -160,3 +160,27 @@ out.append(names())
     assert "weno_flist3d_kernel" not in every
     assert [n for n in ctx if "reset" not in n] == [n for n in every if "reset" not in n]
     assert "weno_flist3d_kernel" in hybrid and "weno_flist3d_kernel" in again
+
+
+@pytest.mark.parametrize("shape,zchunk", [((1, 100_000_000, 2), 1), ((2, 3, 90_000_000), 1), ((3, 70_000_000, 2), 0),
+                                          ((64, 50, 40), 1), ((64, 50, 40), 2_000_000_000)])
+def test_3d_march_lengths_launch(host_calls, shape, zchunk):
+    """Any tuned length of the marches along y and z launches: every cell has
+    its lane, within the runtime's limit."""
+    rcs, ls = host_calls(f'''
+h = create({shape}, hybrid=2)
+assert L.weno_l2is_tune(h, 0, {zchunk}, 0) == 0
+stub.stub_clear()
+rcs = [L.weno_l2is_rhs_ctx(h, U, V), L.weno_l2is_step(h, U, 1e-9)]
+out = [rcs, launches()]
+''')
+    nx, ny, nz = shape
+    assert rcs == [0, 0]
+    marches = [r for r in ls if "weno3d_march_kernel" in r[0]]
+    assert len(marches) == 8
+    for name, gx, gy, gz, threads in marches:
+        assert gx * threads < 1 << 32 and (gy, gz, threads) == (1, 1, 64)
+        groups, n = (-(-nx * nz // 64), ny) if name.split(",")[1].strip() == "1" else (-(-nx * ny // 64), nz)
+        assert gx % groups == 0 and 1 <= gx // groups <= n
+        if zchunk == 1 and groups * n * 64 < 1 << 32:
+            assert gx == groups * n
