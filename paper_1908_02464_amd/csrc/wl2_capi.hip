@@ -283,7 +283,7 @@ hipError_t launch_lf(const weno_l2is_ctx* c, const double* U, double tc) {
 // advance() of a 1D grid keeps a step's stages on the chip (not with global
 // Lax-Friedrichs speeds, which need a grid-wide reduction per stage).
 bool use_line(const weno_l2is_ctx* c) {
-  return c->dim == 1 && use_row(c) && c->p.split != WL2_SPLIT_LF;
+  return c->dim == 1 && use_row(c) && c->p.split != WL2_SPLIT_LF && c->n[0] <= LINE_MAX_CELLS;
 }
 
 // Up to 504 cells every step runs in one workgroup (whose time step knows no

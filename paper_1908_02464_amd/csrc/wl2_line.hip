@@ -38,6 +38,7 @@ hipError_t line_steps(double* U, StepCtl* ctl, double cfl_dx, int n_steps, const
 hipError_t line_advance(double* U, double* tmp, LineCtl* lc, StepCtl* ctl, double cfl_dx, double s_floor,
                         int n_steps, double t_end, const KGrid& g, const KPhys& ph, hipStream_t stream) {
   const int n = g.n[0];
+  if (g.n[1] != 1 || g.n[2] != 1 || n > LINE_MAX_CELLS) return hipErrorInvalidValue;
   hipLaunchKernelGGL(line_begin_kernel, dim3(1), dim3(64), 0, stream, lc, ctl, t_end);
   if (n_steps < 1) return hipGetLastError();
   const int rb = (n + RED_BLOCK - 1) / RED_BLOCK;

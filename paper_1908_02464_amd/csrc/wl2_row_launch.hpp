@@ -64,9 +64,10 @@ hipError_t tile2d_launch(const RowLaunch& L, int rows);
 // 1D grids: n_steps clock steps of U (SSP-RK3, device CFL dt, the clock rule
 // of finalize_dt_kernel; not with global LF splitting, whose speeds need a
 // grid-wide reduction per stage).  line_steps: up to 504 cells, one
-// single-workgroup launch for all steps (no inflow side).  line_advance: any
-// grid, one launch per step; tmp: a second state array.
+// single-workgroup launch for all steps (no inflow side).  line_advance: up to
+// LINE_MAX_CELLS, one launch per step; tmp: a second state array.
 constexpr int LINE_STEPS_MAX_CELLS = 504;
+constexpr int LINE_MAX_CELLS = 0x7fffffff - (1 << 20);  // their 32-bit positions run on past the last cell
 constexpr size_t LINE_CTL_BYTES = 3 * CFL_SLOTS * 128 + 128;
 struct LineCtl;
 hipError_t line_steps(double* U, StepCtl* ctl, double cfl_dx, int n_steps, const KGrid& g, const KPhys& ph,

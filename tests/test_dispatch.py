@@ -184,3 +184,28 @@ out = [rcs, launches()]
         assert gx % groups == 0 and 1 <= gx // groups <= n
         if zchunk == 1 and groups * n * 64 < 1 << 32:
             assert gx == groups * n
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+def test_longest_1d_grids(host_calls, bc):
+    """advance() of 1D grids near 2^31 cells (223 GB with their context): those
+    whose positions would run past 2^31 in the whole-step kernels take the
+    stage kernels."""
+    out = host_calls(f'''
+out = []
+for n in (505, (1 << 31) - 1 - (1 << 20), (1 << 31) - (1 << 20)):
+    h = create((n, 1, 1), bc=[{bc}, {bc}, 1, 1, 1, 1])
+    stub.stub_clear()
+    rc = L.weno_l2is_advance(h, U, 3, 1.0)
+    out.append([n, rc, launches()])
+''')
+    for n, rc, ls in out:
+        assert rc == 0
+        line = [r for r in ls if "line_step_kernel" in r[0]]
+        stage = [r for r in ls if "row_kernel<3" in r[0]]
+        assert (len(line), len(stage)) == ((3, 0) if n < (1 << 31) - (1 << 20) else (0, 9))
+        for name, gx, _, _, threads in ls:  # a lane's first index and one stride beyond the grid
+            if "line_cfl" in name:
+                assert n + gx * threads < 1 << 31
+        for _, gx, _, _, threads in line:
+            assert gx == -(-n // 46) and gx * 46 + 64 < 1 << 31 and gx * threads < 1 << 32
