@@ -122,8 +122,9 @@ int weno_l2is_params_default(weno_l2is_params *p, int nx, int ny, int nz,
  * 2D grids with global LF splitting, 12.4 KB for 1D grids), for 2D
  * grids of 131072 cells or more the face-once correction buffers (68 bytes
  * per cell), and for 3D grids the running sums of the directions (80 bytes
- * per cell) with every face WENO, or with the hybrid switch (per field or
- * per face) a face buffer (120 bytes per cell) and the lists of the faces
+ * per cell; not needed with splittings other than LLF, and left out there
+ * where no room for a state would remain) with every face WENO, or with the
+ * hybrid switch (per field or per face) a face buffer (120 bytes per cell) and the lists of the faces
  * that need the WENO flux (12 bytes per cell).  About 4.4 GB for a 256^3
  * grid with the hybrid switch (3.5 GB with every face WENO, 2.2 GB with
  * every face linear). */

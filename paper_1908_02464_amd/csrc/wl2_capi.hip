@@ -656,21 +656,10 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
          hipMalloc(&c->fo_map, sizeof(unsigned int) * (size_t)c->ncell) == hipSuccess &&
          // every map value stays a valid entry index (< ncell) from the start
          hipMemsetAsync(c->fo_map, 0, sizeof(unsigned int) * (size_t)c->ncell, c->stream) == hipSuccess;
-  // 3D: with every face WENO the running sums of the
-  // directions (10 doubles per cell); with the hybrid switch the corrections
-  // compute each face once into a face buffer (15 doubles per cell), located
-  // by face lists (3 entries per cell)
+  // 3D with the hybrid switch: the corrections compute each face once into a
+  // face buffer (15 doubles per cell), located by face lists (3 entries per cell)
   const bool hyb3 = c->dim == 3 && (p->hybrid == WL2_HYB_PER_FIELD || p->hybrid == WL2_HYB_PER_FACE);
-  const bool weno3 = c->dim == 3 && p->hybrid == WL2_HYB_WENO_ONLY && nx <= WENO3D_MAX_NX;
-  if (ok && (weno3 || hyb3)) {
-    ok = hipMalloc(&c->fo3, sizeof(double) * (weno3 ? 10 * (size_t)c->ncell : fused3d_face_doubles(c->n))) ==
-         hipSuccess;
-    if (!ok && weno3 && p->split != WL2_SPLIT_LLF) {  // too large for the sums: corrections per cell
-      (void)hipGetLastError();
-      c->fo3 = nullptr;
-      ok = true;
-    }
-  }
+  if (ok && hyb3) ok = hipMalloc(&c->fo3, sizeof(double) * fused3d_face_doubles(c->n)) == hipSuccess;
   if (ok && hyb3)
     ok = hipMalloc(&c->flist, sizeof(unsigned int) * fused3d_flist_entries(c->n)) == hipSuccess;
   if (ok && c->dim == 2 && p->split == WL2_SPLIT_LF)
@@ -689,6 +678,22 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
   if (ok && c->dim == 3)
     ok = hipMalloc(&c->counts, sizeof(unsigned int) * (8 * fused3d_count_entries(c->n) + 2)) ==
          hipSuccess;
+  // 3D with every face WENO: the running sums of the directions (10 doubles per
+  // cell).  Splittings other than LLF do without them, by per-cell corrections,
+  // where they leave no room for the caller's state; so they come last.
+  if (ok && c->dim == 3 && p->hybrid == WL2_HYB_WENO_ONLY && nx <= WENO3D_MAX_NX) {
+    const size_t sums = sizeof(double) * 10 * (size_t)c->ncell;
+    const bool must = p->split == WL2_SPLIT_LLF;
+    size_t avail = 0, total = 0;
+    if (must || hipMemGetInfo(&avail, &total) != hipSuccess || (avail >= sums && avail - sums >= bytes)) {
+      ok = hipMalloc(&c->fo3, sums) == hipSuccess;
+      if (!ok && !must) {
+        (void)hipGetLastError();
+        c->fo3 = nullptr;
+        ok = true;
+      }
+    }
+  }
   if (ok) ok = hipMemsetAsync(c->ctl, 0, sizeof(StepCtl), c->stream) == hipSuccess;
   if (!ok) {
     (void)hipFree(c->U1);

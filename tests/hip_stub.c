@@ -54,6 +54,11 @@ int hipFree(void *p) {
     }
   return OK;
 }
+int hipMemGetInfo(size_t *avail, size_t *total) {
+  *avail = capacity - used;
+  *total = capacity;
+  return OK;
+}
 int hipHostMalloc(void **p, size_t n, unsigned flags) {
   (void)flags;
   return (*p = calloc(1, n ? n : 1)) ? OK : OUT_OF_MEMORY;

@@ -209,3 +209,35 @@ for n in (505, (1 << 31) - 1 - (1 << 20), (1 << 31) - (1 << 20)):
                 assert n + gx * threads < 1 << 31
         for _, gx, _, _, threads in line:
             assert gx == -(-n // 46) and gx * 46 + 64 < 1 << 31 and gx * threads < 1 << 32
+
+
+@pytest.mark.parametrize("split", [1, 2])
+def test_3d_sums_leave_room(host_calls, split):
+    """3D with every face WENO and a splitting other than LLF: where the running
+    sums, with what else the context needs and the caller's state, do not fit
+    the device, create() keeps the per-cell corrections; with the memory that
+    those need it succeeds."""
+    out = host_calls(f'''
+shape, n = (64, 60, 50), 64 * 60 * 50
+def used(capacity, expect=0, **kw):
+    stub.stub_capacity(capacity)
+    h = create(shape, hybrid=2, split={split}, expect=expect)
+    if expect:
+        return stub.stub_used()
+    u = stub.stub_used()
+    stub.stub_capacity(1 << 62)
+    stub.stub_clear()
+    assert L.weno_l2is_step(h, U, 1e-9) == 0
+    march = any("weno3d_x" in r[0] for r in launches())
+    L.weno_l2is_destroy(h)
+    return [u, march]
+full = used(1 << 62)
+cells = full[0] - 80 * n
+out = [full, cells]
+out += [used(c) for c in (full[0] + 40 * n, full[0] + 40 * n - 1, full[0], full[0] - 1, cells)]
+out.append(used(cells - 1, expect=capi.E_NOMEM))
+''')
+    full, cells, room, less, tight, short, least, refused = out
+    assert full[1] and room == full
+    assert less == tight == short == least == [cells, False]
+    assert refused == 0
