@@ -121,7 +121,9 @@ int weno_l2is_params_default(weno_l2is_params *p, int nx, int ny, int nz,
  * correction list (8 bytes per cell), a 6.4 KB control block (6 KB more for
  * 2D grids with global LF splitting, 12.4 KB for 1D grids), for 2D
  * grids of 131072 cells or more the face-once correction buffers (68 bytes
- * per cell), and for 3D grids the running sums of the directions (80 bytes
+ * per cell; below 458752 cells and with every face WENO they serve rows set by
+ * weno_l2is_tune only, and are left out where no room for a state would
+ * remain), and for 3D grids the running sums of the directions (80 bytes
  * per cell; not needed with splittings other than LLF, and left out there
  * where no room for a state would remain) with every face WENO, or with the
  * hybrid switch (per field or per face) a face buffer (120 bytes per cell) and the lists of the faces

@@ -651,11 +651,6 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
             hipMalloc(&c->acc, bytes) == hipSuccess &&
             hipMalloc(&c->ctl, sizeof(StepCtl)) == hipSuccess;
   if (ok) ok = hipMalloc(&c->list, sizeof(unsigned long long) * (size_t)c->ncell) == hipSuccess;
-  if (ok && c->dim == 2 && c->ncell >= FACE_ONCE_MIN_CELLS && c->ncell <= 0xffffffffll)
-    ok = hipMalloc(&c->fo_D, sizeof(double) * 2 * c->nvar * (size_t)c->ncell) == hipSuccess &&
-         hipMalloc(&c->fo_map, sizeof(unsigned int) * (size_t)c->ncell) == hipSuccess &&
-         // every map value stays a valid entry index (< ncell) from the start
-         hipMemsetAsync(c->fo_map, 0, sizeof(unsigned int) * (size_t)c->ncell, c->stream) == hipSuccess;
   // 3D with the hybrid switch: the corrections compute each face once into a
   // face buffer (15 doubles per cell), located by face lists (3 entries per cell)
   const bool hyb3 = c->dim == 3 && (p->hybrid == WL2_HYB_PER_FIELD || p->hybrid == WL2_HYB_PER_FACE);
@@ -678,14 +673,39 @@ int weno_l2is_create(int nx, int ny, int nz, double dx, double gamma, const weno
   if (ok && c->dim == 3)
     ok = hipMalloc(&c->counts, sizeof(unsigned int) * (8 * fused3d_count_entries(c->n) + 2)) ==
          hipSuccess;
+  // Buffers that a context can do without come last, and where the caller's
+  // state would no longer fit beside them not at all.
+  const auto room = [bytes](size_t b) {
+    size_t avail = 0, total = 0;
+    return hipMemGetInfo(&avail, &total) != hipSuccess || (avail >= b && avail - b >= bytes);
+  };
+  // 2D: the face-once corrections of the row kernel.  Where the tile kernel
+  // serves the grid, only rows per item asked for by tune() and, on a cached
+  // right-hand-side context, a later scheme lead to them, and per-cell
+  // corrections give the same bits.
+  if (ok && c->dim == 2 && c->ncell >= FACE_ONCE_MIN_CELLS && c->ncell <= 0xffffffffll) {
+    const size_t nc = (size_t)c->ncell, changes = sizeof(double) * 2 * c->nvar * nc, map = sizeof(unsigned int) * nc;
+    const bool must = !use_tile(c);
+    if (must || room(changes + map)) {
+      ok = hipMalloc(&c->fo_D, changes) == hipSuccess && hipMalloc(&c->fo_map, map) == hipSuccess &&
+           // every map value stays a valid entry index (< ncell) from the start
+           hipMemsetAsync(c->fo_map, 0, map, c->stream) == hipSuccess;
+      if (!ok && !must) {
+        (void)hipGetLastError();
+        (void)hipFree(c->fo_D);
+        (void)hipFree(c->fo_map);
+        c->fo_D = nullptr;
+        c->fo_map = nullptr;
+        ok = true;
+      }
+    }
+  }
   // 3D with every face WENO: the running sums of the directions (10 doubles per
-  // cell).  Splittings other than LLF do without them, by per-cell corrections,
-  // where they leave no room for the caller's state; so they come last.
+  // cell).  Splittings other than LLF do without them, by per-cell corrections.
   if (ok && c->dim == 3 && p->hybrid == WL2_HYB_WENO_ONLY && nx <= WENO3D_MAX_NX) {
     const size_t sums = sizeof(double) * 10 * (size_t)c->ncell;
     const bool must = p->split == WL2_SPLIT_LLF;
-    size_t avail = 0, total = 0;
-    if (must || hipMemGetInfo(&avail, &total) != hipSuccess || (avail >= sums && avail - sums >= bytes)) {
+    if (must || room(sums)) {
       ok = hipMalloc(&c->fo3, sums) == hipSuccess;
       if (!ok && !must) {
         (void)hipGetLastError();

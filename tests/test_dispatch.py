@@ -241,3 +241,38 @@ out.append(used(cells - 1, expect=capi.E_NOMEM))
     assert full[1] and room == full
     assert less == tight == short == least == [cells, False]
     assert refused == 0
+
+
+@pytest.mark.parametrize("nx,ny,kw,tile", [(500, 400, {}, True), (900, 700, {"hybrid": 2}, True), (900, 700, {}, False)])
+def test_2d_face_once_buffers_leave_room(host_calls, nx, ny, kw, tile):
+    """The face-once buffers of a 2D grid that the tile kernel serves are not
+    needed: short of memory a context does without them, and with rows set by
+    tune() takes per-cell corrections then."""
+    out = host_calls(f'''
+shape, n = ({nx}, {ny}, 1), {nx} * {ny}
+def used(capacity, expect=0):
+    stub.stub_capacity(capacity)
+    h = create(shape, expect=expect, **{kw!r})
+    if expect:
+        return [stub.stub_used(), None, None]
+    u = stub.stub_used()
+    stub.stub_capacity(1 << 62)
+    kinds = []
+    for rows in (0, 5):
+        assert L.weno_l2is_tune(h, 0, rows, 0) == 0
+        stub.stub_clear()
+        assert L.weno_l2is_step(h, U, 1e-9) == 0
+        names = " ".join(r[0] for r in launches())
+        kinds.append("tile" if "tile2d" in names else "face" if "row_face" in names else "cell")
+    L.weno_l2is_destroy(h)
+    return [u, *kinds]
+full = used(1 << 62)
+out = [n, full, used(full[0] + 32 * n), used(full[0] + 32 * n - 1, 0), used(full[0], 0)]
+out.append(used(full[0] - 1, {0 if tile else -6}))
+''')
+    n, full, room, less, tight, short = out
+    assert full[1:] == ["tile" if tile else "face", "face"] and room == full
+    if tile:
+        assert less == tight == short == [full[0] - 68 * n, "tile", "cell"]
+    else:
+        assert less == tight == full and short[0] == 0
