@@ -476,11 +476,11 @@ int weno_l2is_batch_tune(weno_l2is_batch* b, int rows, int blocks) {
   if (!b) return WL2_E_NULL;
   if (rows < 0 || rows > ROW_MAX_YCH) return WL2_E_PARAM;
   if (blocks != 0 && (blocks < 64 || blocks > 65536)) return WL2_E_PARAM;
-  if (rows && rows != b->rows) {
-    b->rows = rows;
+  if (rows && tile_rows(rows) != tile_rows(b->rows)) {
     b->dirty = true;  // the 2D items follow the rows per item
     drop_graphs(b);   // and so does the build of the stage kernels
   }
+  if (rows) b->rows = rows;
   if (blocks && blocks != b->row_blocks) {
     b->row_blocks = blocks;
     drop_graphs(b);  // the grid size is part of the captured launches

@@ -276,3 +276,24 @@ out.append(used(full[0] - 1, {0 if tile else -6}))
         assert less == tight == short == [full[0] - 68 * n, "tile", "cell"]
     else:
         assert less == tight == full and short[0] == 0
+
+
+def test_batch_rows_name_two_builds(host_calls):
+    """The rows that the autotuner tries each have their build of the stage
+    kernels, and a value that names the build in use captures nothing."""
+    out = host_calls(BATCH + r'''
+from paper_1908_02464_amd import autotune
+admit(0)
+out = []
+for rows in autotune.BATCH_ROWS + (3, 4, 16, 62, 2, 1, 0):
+    assert L.weno_l2is_batch_tune(b, rows, 0) == 0
+    stub.stub_clear()
+    assert L.weno_l2is_batch_advance(b, 1) == 0
+    out.append([rows, sum(l == "capture" for l in log(False)), sorted({n for n, *_ in launches() if "batch_stage" in n})])
+out = [len(autotune.BATCH_ROWS), out]
+L.weno_l2is_batch_destroy(b)
+''')
+    n, runs = out
+    builds = [tuple(k) for _, c, k in runs[:n]]
+    assert all(c == 1 for _, c, _ in runs[:n]) and len(set(builds)) == n
+    assert [c for _, c, _ in runs[n:]] == [0, 0, 0, 0, 1, 0, 0]
