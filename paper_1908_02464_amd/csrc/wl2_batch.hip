@@ -372,8 +372,6 @@ int weno_l2is_batch_admit(weno_l2is_batch* b, int nx, int ny, int nz, double dx,
   double* const dU = (double*)(b->pool + si.off);
   G.cfl_dx = p->cfl * dx;
   G.dim = si.dim;
-  G.nv = si.nvar;
-  G.active = 1;
   StepCtl& C = b->h_ctl[s];
   std::memset(&C, 0, sizeof(C));
   C.t = 0.0;
@@ -465,7 +463,6 @@ int weno_l2is_batch_fetch(weno_l2is_batch* b, int slot, double* U_out, int out_o
   if (steps) *steps = C.steps;
   pool_free(b, si.off, si.bytes);
   si.used = false;
-  b->h_grids[slot].active = 0;
   b->active--;
   b->dirty = true;
   b->state_pending = false;  // snapshots before this retirement are stale

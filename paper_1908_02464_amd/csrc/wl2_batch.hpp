@@ -25,9 +25,7 @@ struct BGrid {
   long long U1;  // stage buffers
   long long U2;
   double cfl_dx;
-  int dim, nv;
-  int active;
-  int pad;
+  int dim;
 };
 
 constexpr int BATCH_MAX_SLOTS = 4096;
@@ -53,8 +51,9 @@ struct BChunks {
 // 1D run (U to U1), in stage 1 its copy back (other items still read U before).
 // FAST: every admitted run has the default scheme (LLF splitting, per-field
 // switch, Eq.(28)), fixed at compile time; else the build that reads it at run
-// time serves them all (the same bits; both in one kernel spill: 52 us per
-// stage against 48).
+// time, which spills, serves them all (the same bits; 28 1D and 12 2D runs, us
+// per step: all default 165, one 2D run of another scheme 224, all 2D runs 201;
+// both codes in one kernel spill as well: 52 us per stage against 48).
 template <int R, int STAGE, bool FAST>
 __global__ __launch_bounds__((2 * R + 1) * 64, 4) void batch_stage_kernel(
     const BGrid* __restrict__ grids, double* pool, StepCtl* ctls, const BatchItem* __restrict__ items1,

@@ -163,9 +163,16 @@ bool use_row(const weno_l2is_ctx* c) { return c->dim <= 2 && c->path != WL2_PATH
 // faces all take the WENO flux, else grids below TILE_MAX_CELLS, where launches
 // and the chain of a stage set the time, not its work.  Measured us per step,
 // tile against row kernel and corrections (four quadrants, LLF / global LF):
-// 64^2 33 against 51 / 38 against 61, 256^2 40, 65 / 44, 74, 512^2 72, 97 / 90,
-// 107, 640^2 98, 106 / 121, 116, 724^2 120, 116 / 148, 125, 1024^2 203, 155;
-// every face WENO at 1024^2 644 / 1251.  A tuned rows-per-item or per-cell
+// 64^2 33 against 51 / 38 against 61, 256^2 40, 65 / 44, 74, 512^2 69, 96 / 87,
+// 106, 640^2 94, 108 / 119, 118, 676^2 98, 110 / 123, 122, 724^2 120, 116 / 148,
+// 125, 1024^2 203, 155; every face WENO at 1024^2 644 / 1251.  Roe splitting, the
+// switch per face and the comparison weightings lie with LLF (676^2 99 against
+// 105, 102 against 110, 102 against 110).  The line is theirs: with global LF and
+// a scheme read at run time the two meet at 580^2 (676^2 130 against 121, but a
+// right-hand side without face-once buffers 38 against 40), with every face
+// linear, where the row kernel has one launch as well, at 512^2 (676^2 91 against
+// 72), and a narrow grid pays for its last column of tiles (340 x 1300 LLF 107
+// against 112, LF 134 against 124).  A tuned rows-per-item or per-cell
 // corrections (WL2_PATH_FUSED_CELLS) ask for the row kernel, whose column offsets
 // have 32 bits: a wider grid takes the tile kernel all the same (the same bits).
 constexpr long long TILE_MAX_CELLS = 7ll << 16;

@@ -172,9 +172,9 @@ __device__ __forceinline__ double cfl_take_wave(StepCtl* ctl) {
 // stage-1 kernel itself (all of its lanes call; every wavefront reads the
 // same slots and clock, so gets the same bits).  The lane with writer set
 // records t0 = t, dt and the step count; it leaves t and the slots alone,
-// which other wavefronts still read: the stage's correction kernel sets
-// t = t0 + dt (the same value as t + dt) and clears the slots
-// (clock_commit).
+// which other wavefronts still read: the stage's correction kernel, or stage 2
+// where the corrections are in place, sets t = t0 + dt (the same value as t +
+// dt) and clears the slots (clock_commit), of a stopped step (dt = 0) as well.
 __device__ __forceinline__ double clock_dt_wave(StepCtl* ctl, double cfl_dx, double s_floor,
                                                 bool writer) {
   double smax = cfl_peek_wave(ctl);

@@ -151,7 +151,8 @@ struct FaceSums {
 // KPhys::inv_dx60).  Cells are requested in the pairs (0,5), (1,4), (2,3) so
 // only two are live at a time.  ANY: returns whether the detector of some
 // field asks for the nonlinear flux (the largest |dv| decides: the square of
-// a product is monotonic in it, so this agrees with the mask bit for bit);
+// a product is monotonic in it, so for finite values this agrees with the mask
+// bit for bit; a face with a NaN among them has a NaN flux, listed or not);
 // else the mask of those fields.
 // The dissipation R (alpha dv): the entropy and shear fields share one
 // splitting speed a0 and sum_s R^s L^s = 1, so it is a0 dU5 plus the two
@@ -314,15 +315,7 @@ __device__ __forceinline__ double weno_l2is_lr(double fm2, double fm1, double f0
   return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * fast_rcp((a0 + a1) + (a2 + a3));
 }
 
-// Nonlinear (WENO-L2IS) flux of one flagged face, field by field: for each
-// field k in `mask`, the left eigenvector row L^k is formed, the six stencil
-// cells are projected (Eq.(20)), split (Eq.(21)) and reconstructed
-// (Eq.(22)-(23)); the other fields keep their linear flux.  The fields'
-// fluxes are back-projected (Eq.(24)), and the correction is the difference
-// from the linear face flux: where that is large and the WENO flux small
-// (ambient cells next to a Mach 2000 jet), the sum of both keeps the
-// rounding of the small one.  Only one row and twelve split values are live.
-// W: the weighting (W_*) fixed at compile time, or -1 to read ph.weights.
+// The products of a shear row: the density's and component i's.
 template <int NV>
 __device__ __forceinline__ double dot2(const double (&r)[NV], const double (&x)[NV], int i) {
   double a = r[0] * x[0];  // the order of dot
@@ -331,8 +324,9 @@ __device__ __forceinline__ double dot2(const double (&r)[NV], const double (&x)[
 }
 
 // K: the field where it is known at compile time, else -1.  A shear row has
-// two entries, so its products with zero (which change no bit of the sum) are
-// left out.
+// two entries, so its products with zero are left out (they change no bit of a
+// finite sum; a state that is not finite makes the acoustic fields NaN, and with
+// them the face's whole flux, either way).
 template <int NV, int DIR, int W, int K, class Src>
 __device__ __forceinline__ double lean_field_row(const Src& src, const double (&r)[NV], const Roe<NV>& s,
                                                  double al, double dvk, const KPhys& ph) {
@@ -394,11 +388,19 @@ __device__ __forceinline__ void left_row_rt(const Roe<NV>& s, int k, double (&r)
   for (int i = 0; i < NV; ++i) r[i] = acoustic ? ac[i] : (k == 1 ? en[i] : sh[i]);
 }
 
-// The change of the face's flux for the fields in mask: R f - F60 / 60.
-// `early` runs before the last field (a kernel's loads for what follows).
 struct NoHook {
   __device__ __forceinline__ void operator()() const {}
 };
+// Nonlinear (WENO-L2IS) flux of one flagged face, field by field: for each
+// field k in `mask`, the left eigenvector row L^k is formed, the six stencil
+// cells are projected (Eq.(20)), split (Eq.(21)) and reconstructed
+// (Eq.(22)-(23)); the other fields keep their linear flux.  The fields'
+// fluxes are back-projected (Eq.(24)), and the correction is the difference
+// from the linear face flux, R f - F60 / 60: where that is large and the WENO
+// flux small (ambient cells next to a Mach 2000 jet), the sum of both keeps the
+// rounding of the small one.  Only one row and twelve split values are live.
+// W: the weighting (W_*) fixed at compile time, or -1 to read ph.weights.
+// `early` runs before the last field (a kernel's loads for what follows).
 template <int NV, int DIR, int W = -1, class Src, class Hook = NoHook>
 __device__ __forceinline__ void lean_correction(const Src& src, unsigned mask, const FaceState<NV>& st,
                                                 const double (&F60)[NV], const KPhys& ph,

@@ -9,7 +9,7 @@
 // of every row is formed without another load.  The current row plus a
 // three-cell x halo is staged in LDS; lane t computes the x face on the left
 // of column t (64 faces for 63 cells) and the right face of a cell arrives
-// from the next lane by a cross-lane shuffle, so every face flux is computed
+// from the next lane by a lane move, so every face flux is computed
 // once and both neighbours use the same bits.  Faces whose detector asks for
 // the nonlinear flux are only flagged in the march: their cells go to a
 // correction list and a separate kernel adds the WENO-L2IS part (one thread

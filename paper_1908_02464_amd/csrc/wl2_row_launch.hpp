@@ -7,7 +7,7 @@
 namespace wl2 {
 
 constexpr int ROW_TILE = 63;     // columns per work item (one wavefront)
-constexpr int ROW_MAX_YCH = 62;  // rows per work item (flag bits per row)
+constexpr int ROW_MAX_YCH = 62;  // rows per work item (the range that tune() states)
 constexpr int ROW_MAX_NX = 1 << 29;  // columns of a 2D grid: a 32-bit byte offset
 
 struct YGhostRule;
