@@ -56,6 +56,7 @@ struct weno_l2is_ctx {
   // both are cleared before the first stage and after a failed launch
   int list_par = 0;
   bool list_dirty = true;
+  bool captured = false;  // a stage was captured into a graph (ListTurn)
   // optional per-launch event timing
   bool timing;
   std::vector<hipEvent_t> ev_pool;
@@ -318,7 +319,11 @@ int row_ych(const weno_l2is_ctx* c) {
   return balanced_chunk((c->n[0] + ROW_TILE - 1) / ROW_TILE, c->n[1], 2, 20);
 }
 
-// The counters of the next stage launch, clearing both if needed.
+// The counters of the next stage launch, clearing both if needed.  A captured
+// stage always clears them, and so does every later one of its context: replays
+// leave the counters as the graph's last stage does, which the host does not
+// follow (a list that starts with a replay's entries corrects their cells again,
+// and can run past its end).
 struct ListTurn {
   weno_l2is_ctx* c;
   unsigned int* cur;
@@ -327,7 +332,10 @@ struct ListTurn {
   explicit ListTurn(const weno_l2is_ctx* cc) : c(const_cast<weno_l2is_ctx*>(cc)) {
     cur = &c->ctl->list_n[c->list_par];
     next = &c->ctl->list_n[c->list_par ^ 1];
-    reset = c->list_dirty;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    if (st != hipStreamCaptureStatusNone) c->captured = true;
+    reset = c->list_dirty || c->captured;
   }
   // after the stage's launches: flip on success, clear both next time if not
   hipError_t done(hipError_t e) {

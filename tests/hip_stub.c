@@ -137,6 +137,9 @@ int hipStreamDestroy(void *s) { (void)s; return OK; }
 int hipStreamSynchronize(void *s) { (void)s; note("sync\n"); return OK; }
 int hipStreamBeginCapture(void *s, int m) { (void)s; (void)m; note("capture\n"); return OK; }
 int hipStreamEndCapture(void *s, void **g) { (void)s; *g = (void *)(uintptr_t)0x2000; return OK; }
+static int capturing;
+void stub_capturing(int on) { capturing = on; }
+int hipStreamIsCapturing(void *s, int *status) { (void)s; *status = capturing; return OK; }
 static uintptr_t n_exec;
 int hipGraphInstantiate(void **e, void *g, void **n, char *l, size_t z) {
   (void)g; (void)n; (void)l; (void)z;

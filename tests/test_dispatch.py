@@ -297,3 +297,27 @@ L.weno_l2is_batch_destroy(b)
     builds = [tuple(k) for _, c, k in runs[:n]]
     assert all(c == 1 for _, c, _ in runs[:n]) and len(set(builds)) == n
     assert [c for _, c, _ in runs[n:]] == [0, 0, 0, 0, 1, 0, 0]
+
+
+@pytest.mark.parametrize("shape,kw", [((900, 1, 1), {"hybrid": 2}), ((900, 1, 1), {"split": 1}), ((800, 700, 1), {}),
+                                      ((24, 20, 18), {})])
+def test_captured_stages_clear_their_lists(host_calls, shape, kw):
+    """A stage with a correction list that is captured into a graph clears the
+    list's counters itself, since a replay starts from what the last one left;
+    so does every stage of that context afterwards, and none before."""
+    out = host_calls(f'''
+h = create({shape}, **{kw!r})
+def calls():
+    stub.stub_clear()
+    assert [L.weno_l2is_rhs_ctx(h, U, V), L.weno_l2is_step(h, U, 1e-9)] == [0, 0]
+    return ["reset" if "reset" in n else "stage" for n, *_ in launches()
+            if "reset" in n or "row_kernel" in n or "fused3d_kernel" in n]
+out = [calls(), calls()]
+stub.stub_capturing(1)
+out.append(calls())
+stub.stub_capturing(0)
+out.append(calls())
+''')
+    first, eager, captured, after = out
+    assert first == ["reset"] * 2 + ["stage"] * 4 and eager == ["stage"] * 4
+    assert captured == after == (["reset"] * 2 + ["stage"]) * 4
