@@ -30,7 +30,7 @@ hipError_t tile2d_launch(const RowLaunch& L, int rows) {
   if (L.rule != nullptr) ta.rule = *L.rule;
   ta.dx = L.dx;
   ta.tc = L.tc;
-  const int tiles_x = (L.g.n[0] + RT - 1) / RT;
+  const unsigned tiles_x = (unsigned)((L.g.n[0] + RT - 1) / RT);
   const long long blocks = (long long)tiles_x * ((L.g.n[1] + rows - 1) / rows);
   if (blocks < 1 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   // a launch holds at most 2^32 - 1 lanes (9.6 M tiles): more go in several
@@ -56,7 +56,7 @@ hipError_t tile2d_launch(const RowLaunch& L, int rows) {
   if (rows != 1 && rows != 3) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
   for (long long f = 0; f < blocks && e == hipSuccess; f += most) {
-    const int first = (int)f;
+    const unsigned first = (unsigned)f;
     const dim3 gr((unsigned)(blocks - f < most ? blocks - f : most));
     if (rows == 1) WL2_TILE_OUT(1);
     else WL2_TILE_OUT(3);

@@ -215,13 +215,14 @@ __device__ __forceinline__ void tile2d_item(const TileArgs& ta, const KGrid& g, 
   }
 }
 
-// Tiles first + blockIdx.x.
+// Tiles first + blockIdx.x (unsigned: a signed division costs each wavefront's
+// start 0.2 us).
 template <int R, int OUT, int SPLIT, int HYB, int W>
 __global__ __launch_bounds__((2 * R + 1) * 64, 4) void tile2d_kernel(TileArgs ta, KGrid g, KPhys ph,
-                                                                    int tiles_x, int first) {
+                                                                    unsigned tiles_x, unsigned first) {
   __shared__ TileShared<R> sh;
-  const int b = first + (int)blockIdx.x;
-  tile2d_item<R, OUT, SPLIT, HYB, W>(ta, g, ph, (b % tiles_x) * RT, (b / tiles_x) * R, b == 0, sh);
+  const unsigned b = first + blockIdx.x;
+  tile2d_item<R, OUT, SPLIT, HYB, W>(ta, g, ph, (int)(b % tiles_x) * RT, (int)(b / tiles_x) * R, b == 0u, sh);
 }
 
 }  // namespace wl2
