@@ -70,27 +70,20 @@ hipError_t row_fix(const RowLaunch& L) {
 #undef WL2_FO
     return hipGetLastError();
   }
-#define WL2_FIX_BUILD(NV, O, S, H, WPE) \
-  hipLaunchKernelGGL((row_fix_kernel<NV, O, S, H, WPE>), fgc, fb, 0, L.stream, a, L.g, L.ph)
-#define WL2_FIX(NV, O, WPE)                                              \
-  do {                                                                   \
-    if (L.fast == 1) WL2_FIX_BUILD(NV, O, SPLIT_LLF, HYB_PER_FIELD, 2);      \
-    else if (L.fast == 2) WL2_FIX_BUILD(NV, O, SPLIT_LF, HYB_PER_FIELD, 2);  \
-    else WL2_FIX_BUILD(NV, O, -1, -1, WPE);                              \
+  // two wavefronts per SIMD hold 131072 cells
+  if (L.nvar == 3 && L.fast == 0 && L.g.ncell > 131072) return row_fix_three_waves(L, a, fgc, fb);
+#define WL2_FIX_BUILD(NV, O, S, H) \
+  hipLaunchKernelGGL((row_fix_kernel<NV, O, S, H, 2>), fgc, fb, 0, L.stream, a, L.g, L.ph)
+#define WL2_FIX(NV, O)                                                \
+  do {                                                                \
+    if (L.fast == 1) WL2_FIX_BUILD(NV, O, SPLIT_LLF, HYB_PER_FIELD);     \
+    else if (L.fast == 2) WL2_FIX_BUILD(NV, O, SPLIT_LF, HYB_PER_FIELD); \
+    else WL2_FIX_BUILD(NV, O, -1, -1);                                \
   } while (0)
   if (L.nvar == 3) {
-    // two wavefronts per SIMD hold 131072 cells
-    const bool three = L.g.ncell > 131072;
-    if (L.out_kind == OUT_RK) {
-      if (three) WL2_FIX(3, OUT_RK, 3);
-      else WL2_FIX(3, OUT_RK, 2);
-    } else {
-      if (three) WL2_FIX(3, OUT_WRITE, 3);
-      else WL2_FIX(3, OUT_WRITE, 2);
-    }
+    if (L.out_kind == OUT_RK) WL2_FIX(3, OUT_RK); else WL2_FIX(3, OUT_WRITE);
   } else if (L.nvar == 4) {
-    if (L.out_kind == OUT_RK) WL2_FIX(4, OUT_RK, 2);
-    else WL2_FIX(4, OUT_WRITE, 2);
+    if (L.out_kind == OUT_RK) WL2_FIX(4, OUT_RK); else WL2_FIX(4, OUT_WRITE);
   } else {
     return hipErrorInvalidValue;
   }

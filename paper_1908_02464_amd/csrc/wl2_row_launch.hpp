@@ -56,6 +56,9 @@ struct RowLaunch {
 hipError_t row_reset(const RowLaunch& L);
 hipError_t row_launch(const RowLaunch& L);
 hipError_t row_fix(const RowLaunch& L);
+// row_fix of a 1D list whose scheme is read at run time, three wavefronts per SIMD.
+struct RowArgs;
+hipError_t row_fix_three_waves(const RowLaunch& L, const RowArgs& a, dim3 grid, dim3 block);
 
 // 2D: one stage with its corrections in one launch, `rows` (1 or 3) rows per
 // workgroup (list and face-once members unused).
