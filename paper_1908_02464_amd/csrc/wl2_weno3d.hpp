@@ -17,7 +17,8 @@
 // stage, before -> now: 160^3 1180 -> 810, 32^3 100 -> 34, 64^3 160 -> 94, 256^3
 // 4940 -> 3440 (the weights of Eq.(14)-(15) 6080 -> 3530); splittings other
 // than LLF, whose faces were computed for both of their cells, 96^3 489 -> 210.
-// The x kernel issues VALU instructions in 93 % of its cycles.
+// The three kernels issue VALU instructions in 91 to 94 % of their cycles, at
+// 1.84 to 1.89 GHz; 32 to 36 TFLOP/s at 256^3.
 #pragma once
 #include "wl2_fused_launch.hpp"
 #include "wl2_lface.hpp"
