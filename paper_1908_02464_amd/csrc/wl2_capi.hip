@@ -332,8 +332,8 @@ struct ListTurn {
   explicit ListTurn(const weno_l2is_ctx* cc) : c(const_cast<weno_l2is_ctx*>(cc)) {
     cur = &c->ctl->list_n[c->list_par];
     next = &c->ctl->list_n[c->list_par ^ 1];
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;  // (the null stream is never captured)
+    if (c->stream != nullptr && hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
     if (st != hipStreamCaptureStatusNone) c->captured = true;
     reset = c->list_dirty || c->captured;
   }

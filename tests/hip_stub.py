@@ -29,10 +29,10 @@ from paper_1908_02464_amd import capi
 L = capi.lib()
 U, V = 1 << 56, 1 << 58
 
-def create(shape, dx=0.1, expect=0, **kw):
+def create(shape, dx=0.1, expect=0, stream=None, **kw):
     p = capi.params_default(*shape, dx, **kw)
     h = C.c_void_p()
-    rc = L.weno_l2is_create(*shape, dx, 1.4, C.byref(p), None, C.byref(h))
+    rc = L.weno_l2is_create(*shape, dx, 1.4, C.byref(p), C.c_void_p(stream), C.byref(h))
     assert rc == expect, rc
     return h
 

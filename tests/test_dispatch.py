@@ -306,7 +306,7 @@ def test_captured_stages_clear_their_lists(host_calls, shape, kw):
     list's counters itself, since a replay starts from what the last one left;
     so does every stage of that context afterwards, and none before."""
     out = host_calls(f'''
-h = create({shape}, **{kw!r})
+h = create({shape}, stream=1 << 12, **{kw!r})
 def calls():
     stub.stub_clear()
     assert [L.weno_l2is_rhs_ctx(h, U, V), L.weno_l2is_step(h, U, 1e-9)] == [0, 0]
