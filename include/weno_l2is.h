@@ -263,7 +263,8 @@ enum { WL2_PATH_AUTO = 0, WL2_PATH_SWEEPS = 1, WL2_PATH_FUSED = 2, WL2_PATH_FUSE
 int weno_l2is_tune(weno_l2is_ctx *ctx, int path, int zchunk, int waves_per_simd);
 
 /* Per-launch kernel timing with HIP events recorded on the context's stream
- * around every kernel the context enqueues.  enable != 0 starts (and clears)
+ * around every kernel the context enqueues (the launches of one advance call
+ * that run whole steps of a 1D grid count as one).  enable != 0 starts (and clears)
  * collection; 0 stops it.  Costs two event records per launch. */
 int weno_l2is_timing_enable(weno_l2is_ctx *ctx, int enable);
 
