@@ -79,3 +79,5 @@ def test_columns_past_32_bit_offsets():
         a, b = 0 if x == 0 else 3, w if x == nx - w else w - 3  # cells whose stencils lie in the cut
         assert float(E.abs().max()) > 0.01
         assert torch.equal(D[:, :, :, x + a:x + b], E[:, :, :, a:b]), x
+    del U, D, V, E
+    torch.cuda.empty_cache()
